@@ -81,6 +81,11 @@ int ensure_tree_buffers(fdx_ctx *c, uint32_t cell_cap, uint32_t group_cap) {
         HIPCHK(c, c->f_pre.ensure((size_t)group_cap + 1));
         c->group_cap = group_cap;
     }
+    if (c->n > kFarMaxDirect && c->g_near.cap < c->group_cap) {
+        c->gen++;
+        HIPCHK(c, c->g_far.ensure(c->group_cap));
+        HIPCHK(c, c->g_near.ensure(c->group_cap));
+    }
     return FDX_OK;
 }
 
@@ -93,10 +98,20 @@ Cells cells_view(fdx_ctx *c) {
     return v;
 }
 
+// whether the FP32 path expands far superparticles: Newtonian forces, and a system large enough
+// (the entry point that allocates nothing takes no larger one and has no buffers for it)
+static bool use_far(const fdx_ctx *c) {
+    if (!(c->flags & FDX_FP32REL) || (c->flags & FDX_FUSED) || c->cutoff > 0) return false;
+    int64_t largest = 0;
+    for (int s = 0; s < c->nsys && (size_t)s + 1 < c->sys_off_h.size(); s++)
+        largest = std::max(largest, c->sys_off_h[s + 1] - c->sys_off_h[s]);
+    return largest > kFarMaxDirect;
+}
+
 Groups groups_view(fdx_ctx *c) {
     Groups g;
     g.cell = c->g_cell.p; g.begin = c->g_begin.p; g.count = c->g_count.p; g.sys = c->g_sys.p;
-    g.box = c->g_box.p; g.centre = c->g_centre.p; g.wide = c->g_wide.p; g.cap = c->group_cap;
+    g.box = c->g_box.p; g.centre = c->g_centre.p; g.wide = c->g_wide.p; g.far = use_far(c) ? c->g_far.p : nullptr; g.cap = c->group_cap;
     return g;
 }
 
@@ -269,6 +284,8 @@ int enqueue_force(fdx_ctx *c, size_t gmax) {
     fa.bounds = persistent ? c->f_bounds.p : nullptr;
     fa.variant = ext_force_variant(c);
     fa.r_cut = c->cutoff;
+    fa.near = fa.fp32 && gv.far ? c->g_near.p : nullptr;
+    if (fa.near) HIPCHK(c, far_expand(gmax, fa, s));
     HIPCHK(c, force(gmax, fa, s));
     if (fa.fp32) {
         // groups too wide for group-relative FP32: evaluated again by the FP64 kernel, which
@@ -277,6 +294,7 @@ int enqueue_force(fdx_ctx *c, size_t gmax) {
         HIPCHK(c, wide_group_list(gmax, gv, c->wide_list.p, c->st, s));
         ForceArgs fw = fa;
         fw.fp32 = false;
+        fw.near = nullptr;
         fw.persistent = true;
         fw.order = c->wide_list.p;
         fw.count = &c->st->wide_groups;

@@ -11,6 +11,7 @@
 
 #include "../../include/fdx.h"
 #include "abi_guard.h"
+#include "far_field.h"
 #include "fdx_internal.h"
 #include "host_ext.h"
 
@@ -92,6 +93,8 @@ struct fdx_ctx {
     fdx::DBuf<uint32_t> g_wide, wide_list;     // groups evaluated in FP64 by the FP32 path
     fdx::DBuf<uint8_t> leaf_lev;               // level of every sorted particle's leaf
     fdx::DBuf<double> g_centre;
+    fdx::DBuf<fdx::FarGeom> g_far;             // far-field expansion of the FP32 path
+    fdx::DBuf<uint32_t> g_near;
     uint32_t group_cap = 0;
 
     // lists
@@ -144,7 +147,7 @@ struct fdx_ctx {
         f(c_level); f(c_begin); f(c_count); f(c_first); f(c_nchild); f(c_parent); f(c_lvl);
         f(c_prefix); f(c_node); f(c_link); f(c_mom); f(tmp_n); f(tmp_off);
         f(g_cell); f(g_begin); f(g_count); f(g_sys); f(g_box); f(flag); f(gcell_at); f(gpos);
-        f(g_wide); f(wide_list); f(leaf_lev); f(g_centre);
+        f(g_wide); f(wide_list); f(leaf_lev); f(g_centre); f(g_far); f(g_near);
         f(cnt_e); f(cnt_s); f(lcap); f(list); f(ovf_list); f(seg);
         f(f_cost); f(f_bounds); f(f_pre);
         f(fs); f(ax); f(ay); f(az); f(pot);

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 namespace fdx {
 
@@ -166,6 +167,24 @@ __device__ __forceinline__ double row_min_nonneg_f64(double v) {
     o = dpp_move_u64_max_id<0x112, 0xf>(u); u = o < u ? o : u;
     o = dpp_move_u64_max_id<0x114, 0xf>(u); u = o < u ? o : u;
     o = dpp_move_u64_max_id<0x118, 0xf>(u); u = o < u ? o : u;
+    return __longlong_as_double((long long)u);
+}
+
+// maximum of non-negative doubles over each 16-lane row, held by the row's last lane
+__device__ __forceinline__ double row_max_nonneg_f64(double v) {
+    uint64_t u = (uint64_t)__double_as_longlong(v);
+    auto move = [](uint64_t x, auto ctrl) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)(uint32_t)x, decltype(ctrl)::value, 0xf, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)(uint32_t)(x >> 32), decltype(ctrl)::value, 0xf, 0xf, false);
+        return (uint64_t)lo | ((uint64_t)hi << 32);
+    };
+    uint64_t o;
+    o = move(u, std::integral_constant<int, 0x111>{}); u = o > u ? o : u;
+    o = move(u, std::integral_constant<int, 0x112>{}); u = o > u ? o : u;
+    o = move(u, std::integral_constant<int, 0x114>{}); u = o > u ? o : u;
+    o = move(u, std::integral_constant<int, 0x118>{}); u = o > u ? o : u;
     return __longlong_as_double((long long)u);
 }
 

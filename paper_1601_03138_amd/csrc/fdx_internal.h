@@ -54,11 +54,14 @@ struct Cells {
     uint32_t cap;
 };
 
+struct FarGeom;       // far_field.h
+
 struct Groups {
     uint32_t *cell, *begin, *count, *sys;
     uint32_t *box;    // 6 per group: qmin x y z, qmax x y z (grid units)
     double *centre;   // 3 per group: geometric centre of the group's cell
     uint32_t *wide;   // 1 where group-relative FP32 would be too coarse (evaluated in FP64)
+    FarGeom *far;     // geometry of the far-field expansion (null: none is made)
     uint32_t cap;
 };
 
@@ -300,7 +303,7 @@ struct ForceArgs {
     const double *mom;
     const uint64_t *seg;
     const uint32_t *cap, *cnt_e, *cnt_s;
-    const uint32_t *list;   // interaction list segments
+    uint32_t *list;         // interaction list segments
     const uint32_t *order;  // queue order (null: group order)
     const uint32_t *bounds = nullptr;  // persistent launch: the eight per-XCD runs (null: equal
                                        // group counts)
@@ -310,7 +313,13 @@ struct ForceArgs {
     int variant;            // kernel shape chosen by the autotuner
     double r_cut = 0.0;     // > 0: tree part of TreePM (monopole, S2 cutoff), no potential
     const uint32_t *count = nullptr;   // persistent launch: device group count (default: all)
+    uint32_t *near = nullptr;          // FP32: far superparticles come from far_expand, which
+                                       // leaves every group's near count here (kNone: the group
+                                       // is not expanded); null: every pair is evaluated
 };
+// FP32: the field of every group's far superparticles, summed in one polynomial per group, into
+// fs; reorders each expanded group's superparticle list (near ones first) and sets near
+hipError_t far_expand(size_t gmax, const ForceArgs &a, hipStream_t s);
 // G = number of groups (direct launch: one workgroup per group; persistent launch: G bounds
 // the grid and the kernel reads the true count from the device status).
 hipError_t force(size_t G, const ForceArgs &a, hipStream_t s);

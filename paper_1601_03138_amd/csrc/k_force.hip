@@ -49,6 +49,8 @@ struct KArgs {
     DevStatus *st;
     uint32_t G;              // groups (direct launch); persistent kernels read *ngroups
     double cut_s;            // cutoff kernel: 2 / r_cut
+    const uint32_t *near;    // FP32 with a far-field expansion: near superparticles per group
+                             // (kNone: not expanded), or null
 };
 
 // Kahan accumulator (FP32) or plain sum (FP64)
@@ -87,10 +89,17 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
     // the group's values are the same in every lane: held in scalar registers
     gi = uniform_u32(gi);
     const uint32_t gb = uniform_u32(a.gbegin[gi]), ni = uniform_u32(a.gcount[gi]);
-    const uint32_t ne = uniform_u32(a.cnt_e[gi]), ns = uniform_u32(a.cnt_s[gi]);
+    const uint32_t ne = uniform_u32(a.cnt_e[gi]);
+    uint32_t ns = uniform_u32(a.cnt_s[gi]);
     const uint32_t capg = uniform_u32(a.cap[gi]);
     const uint32_t *epj = a.list + uniform_u64(a.seg[gi]);
     const uint32_t *spj = epj + capg - ns;
+    // superparticles evaluated here: the first `near` of the group's when its far ones were
+    // expanded (k_far.hip; their field is in fs), else all
+    constexpr bool FAR = sizeof(T) == 4 && !CUT;
+    const uint32_t near = FAR && a.near ? uniform_u32(a.near[gi]) : kNone;
+    const bool far = FAR && near != kNone;
+    if (far) ns = near;
     const bool fp32 = sizeof(T) == 4;
     const double cx = fp32 ? uniform_f64(a.gcentre[3 * gi]) : 0.0;
     const double cy = fp32 ? uniform_f64(a.gcentre[3 * gi + 1]) : 0.0;
@@ -251,11 +260,12 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
         const uint32_t k = IPL == 1 ? 0u : slot / tps, lk = slot - k * tps;
         const uint32_t i = lk + k * tps;
         if (i >= ni) continue;
-        double v = 0;
+        const uint32_t r = gb + i;
+        // the far field of an expanded group is already there (k_far.hip)
+        double v = FAR && far ? reinterpret_cast<const double *>(a.fs + r)[c] : 0.0;
         const double *o = sm.red + 4 * ((size_t)k * NT + lk) + c;
 #pragma unroll 1
         for (uint32_t q = 0; q < nslice; q++) v += o[4 * (size_t)q * tps];
-        const uint32_t r = gb + i;
         reinterpret_cast<double *>(a.fs + r)[c] = (CUT && c == 3) ? 0.0 : v;
     }
     __syncthreads();
@@ -430,6 +440,7 @@ hipError_t force(size_t G, const ForceArgs &fa, hipStream_t s) {
     k.fs = fa.fs; k.st = fa.st;
     k.G = (uint32_t)G;
     k.cut_s = fa.r_cut > 0 ? 2.0 / fa.r_cut : 0.0;
+    k.near = fa.near;
     if (fa.r_cut > 0) {                // tree part of TreePM: monopole with the S2 cutoff
         if (!fa.fp32) return launch<double, false, 256, 2, false, 1, true>(k, fa.persistent, s);
         // the persistent loop holds the 64-register budget only without the register prefetch

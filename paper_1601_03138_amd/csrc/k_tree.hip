@@ -14,6 +14,7 @@
 // Groups (modified tree algorithm, section "Tree traverse and interaction calculation"):
 // maximal cells of at most n_group particles; an over-full leaf is cut into runs of n_group.
 #include "dev_util.h"
+#include "far_field.h"
 #include "fdx_internal.h"
 
 namespace fdx {
@@ -437,19 +438,22 @@ k_group_geom(const uint32_t *ngroups, int nsys, const int64_t *off, Cells c,
         const uint32_t e = valid ? b + g.count[gi] : 0u;
         uint32_t lo[3] = {kNone, kNone, kNone}, hi[3] = {0, 0, 0};
         uint32_t deep = 0;
-        double emin = INFINITY;
+        double emin = INFINITY, emax = 0.0;
         for (uint32_t r = b + (uint32_t)rl; r < e; r += 16) {
             const uint64_t k = skey[r];
             const uint32_t q[3] = {compact3(k >> 2), compact3(k >> 1), compact3(k)};
 #pragma unroll
             for (int a = 0; a < 3; a++) { lo[a] = min(lo[a], q[a]); hi[a] = max(hi[a], q[a]); }
             deep = max(deep, (uint32_t)plev[r]);
-            emin = fmin(emin, seps[r]);
+            const double ei = seps[r];
+            emin = fmin(emin, ei);
+            emax = fmax(emax, ei);
         }
 #pragma unroll
         for (int a = 0; a < 3; a++) { lo[a] = row_min_u32(lo[a]); hi[a] = row_max_u32(hi[a]); }
         deep = row_max_u32(deep);
         emin = row_min_nonneg_f64(emin);
+        emax = row_max_nonneg_f64(emax);
         if (valid && rl == 15) {
             const int slo = system_of(off, nsys, b);      // last s with off[s] <= b
             const uint32_t cell = g.cell[gi];
@@ -470,7 +474,31 @@ k_group_geom(const uint32_t *ngroups, int nsys, const int64_t *off, Cells c,
             const double side = ldexp(cb[3], -(int)l);
             const double span = ldexp(1.0, (int)deep - (int)l);
             const double m = fmin(side / emin, span);
-            g.wide[gi] = (9.0 * 5.9604644775390625e-8) * m > 1e-4 ? 1u : 0u;
+            const bool wide = (9.0 * 5.9604644775390625e-8) * m > 1e-4;
+            g.wide[gi] = wide ? 1u : 0u;
+            if (g.far) {
+                FarGeom f;
+                double d2 = 0.0, ec[3];
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    const double d = (double)(hi[a] - lo[a]) + 1.0;
+                    d2 += d * d;
+                    ec[a] = cb[a] + (double)(lo[a] + hi[a] + 1u) * h;
+                }
+                f.ex = ec[0]; f.ey = ec[1]; f.ez = ec[2];
+                f.inv_h = 1.0 / side;
+                const double er = emin * f.inv_h;
+                f.e2 = (float)(er * er);
+                // squared box radius: half its diagonal, in units of the cell side and in length
+                const double r2 = ldexp(d2, 2 * ((int)l - 22));
+                f.thr2 = (float)(r2 * side * side * (double)(kFarRatio * kFarRatio));
+                // one softening; scales whose powers stay in range; a deep enough tree
+                const double span = (double)kFarRatio * kFarSpan;
+                if (wide || emin != emax || !(f.inv_h > 1e-15 && f.inv_h < 1e15) ||
+                    !(f.e2 < 1e8f) || r2 * span * span > ldexp(1.0, 2 * (int)l))
+                    f.thr2 = -1.0f;
+                g.far[gi] = f;
+            }
         }
     }
 }
