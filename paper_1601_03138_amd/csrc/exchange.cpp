@@ -18,6 +18,9 @@ constexpr uint64_t kExchangeBudgetBytes = 16ull << 30;
 struct ExchangeState {
     DBuf<uint32_t> box, start, sel, ne, ns, cap, list, nsel, front, fcount;
     DBuf<uint64_t> seg, total;
+    DBuf<uint64_t> oe, os, sums;     // prefix sums of ne and ns, their totals
+    DBuf<uint32_t> pe, ps;           // entries per ordered pair
+    DBuf<uint32_t> out_e, out_s;     // lists in pair order (fdx_get_exchange_lists)
     uint64_t list_cap = 0;
     int nsys = 0;
     size_t pairs = 0;
@@ -30,8 +33,8 @@ struct ExchangeState {
     void release() {
         for (auto *b : {&box, &start, &sel, &ne, &ns, &cap, &list, &nsel, &front, &fcount})
             b->release();
-        seg.release();
-        total.release();
+        for (auto *b : {&seg, &total, &oe, &os, &sums}) b->release();
+        for (auto *b : {&pe, &ps, &out_e, &out_s}) b->release();
         for (auto &e : ev)
             if (e) { (void)hipEventDestroy(e); e = nullptr; }
         list_cap = 0;
@@ -103,6 +106,11 @@ int fdx_build_exchange_lists(fdx_ctx *c, double theta, int32_t n_leaf) {
     HIPCHK(c, x->cap.ensure(G));
     HIPCHK(c, x->seg.ensure(G + 1));
     HIPCHK(c, x->total.ensure(1));
+    HIPCHK(c, x->oe.ensure(G));
+    HIPCHK(c, x->os.ensure(G));
+    HIPCHK(c, x->sums.ensure(2));
+    HIPCHK(c, x->pe.ensure(P));
+    HIPCHK(c, x->ps.ensure(P));
     HIPCHK(c, x->nsel.ensure(1));
     HIPCHK(c, x->front.ensure((size_t)kExchangeFrontierMax * c->nsys));
     HIPCHK(c, x->fcount.ensure(c->nsys));
@@ -140,6 +148,13 @@ int fdx_build_exchange_lists(fdx_ctx *c, double theta, int32_t n_leaf) {
     HIPCHK(c, walk(true, G, pg, cv, th2, x->seg.p, x->cap.p, x->list_cap, x->list.p, x->ne.p,
                    x->ns.p, nullptr, x->sel.p, x->nsel.p, c->st, s));
     HIPCHK(c, hipEventRecord(x->ev[2], s));
+    // where every slot's entries go in the pair-ordered lists, and the pairs' counts
+    HIPCHK(c, scan_u32_to_u64(x->ne.p, x->oe.p, G, nullptr, nullptr, c->partial.p, x->sums.p, s));
+    HIPCHK(c, scan_u32_to_u64(x->ns.p, x->os.p, G, nullptr, nullptr, c->partial.p, x->sums.p + 1,
+                              s));
+    HIPCHK(c, exchange_pairs(P, x->oe.p, x->os.p, x->sums.p, x->pe.p, x->ps.p, s));
+    uint64_t sums[2];
+    HIPCHK(c, hipMemcpyAsync(sums, x->sums.p, sizeof sums, hipMemcpyDeviceToHost, s));
     r = read_status(c);
     if (r) return r;
     const DevStatus &h = c->hst->st;
@@ -149,12 +164,8 @@ int fdx_build_exchange_lists(fdx_ctx *c, double theta, int32_t n_leaf) {
     float t0 = 0, t1 = 0;
     HIPCHK(c, hipEventElapsedTime(&t0, x->ev[0], x->ev[1]));
     HIPCHK(c, hipEventElapsedTime(&t1, x->ev[1], x->ev[2]));
-    std::vector<uint32_t> ne(G), ns(G);
-    HIPCHK(c, hipMemcpyAsync(ne.data(), x->ne.p, 4 * G, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(ns.data(), x->ns.p, 4 * G, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
-    x->n_epj = x->n_spj = 0;
-    for (size_t g = 0; g < G; g++) { x->n_epj += ne[g]; x->n_spj += ns[g]; }
+    x->n_epj = sums[0];
+    x->n_spj = sums[1];
     x->entries = x->n_epj + x->n_spj;
     x->capacity = total;
     x->nsys = c->nsys;
@@ -173,23 +184,16 @@ int fdx_get_exchange_counts(fdx_ctx *c, uint32_t *n_epj, uint32_t *n_spj) {
     int r = check_built(c);
     if (r) return r;
     ExchangeState *x = static_cast<ExchangeState *>(c->ext.exch);
-    const size_t S = (size_t)x->nsys, G = exchange_subwalks(x->nsys);
-    std::vector<uint32_t> ne(G), ns(G);
-    HIPCHK(c, hipMemcpyAsync(ne.data(), x->ne.p, 4 * G, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(ns.data(), x->ns.p, 4 * G, hipMemcpyDeviceToHost, c->stream));
+    const size_t S = (size_t)x->nsys, P = x->pairs;
+    std::vector<uint32_t> pe(P), ps(P);
+    HIPCHK(c, hipMemcpyAsync(pe.data(), x->pe.p, 4 * P, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(ps.data(), x->ps.p, 4 * P, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (size_t s = 0; s < S; s++)
         for (size_t q = 0; q < S; q++) {
-            uint32_t e = 0, sp = 0;
-            if (q != s) {
-                const size_t k = s * (S - 1) + (q < s ? q : q - 1);
-                for (size_t g = k * kExchangeFrontierMax; g < (k + 1) * kExchangeFrontierMax; g++) {
-                    e += ne[g];
-                    sp += ns[g];
-                }
-            }
-            if (n_epj) n_epj[s * S + q] = e;
-            if (n_spj) n_spj[s * S + q] = sp;
+            const size_t k = s * (S - 1) + (q < s ? q : q - 1);
+            if (n_epj) n_epj[s * S + q] = q != s ? pe[k] : 0u;
+            if (n_spj) n_spj[s * S + q] = q != s ? ps[k] : 0u;
         }
     return FDX_OK;
     FDX_ABI_CATCH(c)
@@ -201,35 +205,20 @@ int fdx_get_exchange_lists(fdx_ctx *c, uint32_t *epj, uint32_t *spj) {
     int r = check_built(c);
     if (r) return r;
     ExchangeState *x = static_cast<ExchangeState *>(c->ext.exch);
-    const size_t P = exchange_subwalks(x->nsys), n = (size_t)c->n;   // sub-walks, pair-major
-    std::vector<uint32_t> ne(P), ns(P), cap(P), perm(n);
-    std::vector<uint64_t> seg(P);
+    // pair order on the device, then one copy per kind
     hipStream_t s = c->stream;
-    HIPCHK(c, hipMemcpyAsync(ne.data(), x->ne.p, 4 * P, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(ns.data(), x->ns.p, 4 * P, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(cap.data(), x->cap.p, 4 * P, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(seg.data(), x->seg.p, 8 * P, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(perm.data(), c->sperm, 4 * n, hipMemcpyDeviceToHost, s));
+    const bool want_e = epj && x->n_epj, want_s = spj && x->n_spj;
+    if (!want_e && !want_s) return FDX_OK;
+    if (want_e) HIPCHK(c, x->out_e.ensure(x->n_epj));
+    if (want_s) HIPCHK(c, x->out_s.ensure(x->n_spj));
+    HIPCHK(c, exchange_gather(exchange_subwalks(x->nsys), x->sel.p, x->nsel.p, x->seg.p, x->cap.p,
+                              x->ne.p, x->ns.p, x->oe.p, x->os.p, x->list.p, c->sperm,
+                              want_e ? x->out_e.p : nullptr, want_s ? x->out_s.p : nullptr, s));
+    if (want_e)
+        HIPCHK(c, hipMemcpyAsync(epj, x->out_e.p, 4 * x->n_epj, hipMemcpyDeviceToHost, s));
+    if (want_s)
+        HIPCHK(c, hipMemcpyAsync(spj, x->out_s.p, 4 * x->n_spj, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
-    // each sub-walk's segment: particles from its front, cells from its back; a pair's
-    // entries are its sub-walks' in slot order
-    std::vector<uint32_t> e(std::max<uint64_t>(x->n_epj, 1)), sp(std::max<uint64_t>(x->n_spj, 1));
-    size_t oe = 0, os = 0;
-    for (size_t k = 0; k < P; k++) {
-        if (epj && ne[k])
-            HIPCHK(c, hipMemcpyAsync(e.data() + oe, x->list.p + seg[k], 4 * (size_t)ne[k],
-                                     hipMemcpyDeviceToHost, s));
-        if (spj && ns[k])
-            HIPCHK(c, hipMemcpyAsync(sp.data() + os, x->list.p + seg[k] + cap[k] - ns[k],
-                                     4 * (size_t)ns[k], hipMemcpyDeviceToHost, s));
-        oe += ne[k];
-        os += ns[k];
-    }
-    HIPCHK(c, hipStreamSynchronize(s));
-    if (epj)
-        for (size_t i = 0; i < oe; i++) epj[i] = perm[e[i]];
-    if (spj)
-        for (size_t i = 0; i < os; i++) spj[i] = sp[i];
     return FDX_OK;
     FDX_ABI_CATCH(c)
 }

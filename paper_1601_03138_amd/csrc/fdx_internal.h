@@ -161,6 +161,16 @@ hipError_t exchange_split(int nsys, const Cells c, const uint64_t *bbox_u, const
                           hipStream_t s);
 hipError_t exchange_caps(size_t G, const uint32_t *sel, const uint32_t *nsel, const uint32_t *ne,
                          const uint32_t *ns, uint32_t *cap, hipStream_t s);
+// per-pair counts from the exclusive prefix sums (oe, os; total = {particles, cells}) of the
+// slots' counts, and the active slots' entries gathered in slot order, particles through perm
+// (epj or spj may be null)
+hipError_t exchange_pairs(size_t P, const uint64_t *oe, const uint64_t *os, const uint64_t *total,
+                          uint32_t *pe, uint32_t *ps, hipStream_t s);
+hipError_t exchange_gather(size_t G, const uint32_t *sel, const uint32_t *nsel,
+                           const uint64_t *seg, const uint32_t *cap, const uint32_t *ne,
+                           const uint32_t *ns, const uint64_t *oe, const uint64_t *os,
+                           const uint32_t *list, const uint32_t *perm, uint32_t *epj,
+                           uint32_t *spj, hipStream_t s);
 size_t exchange_subwalks(int nsys);
 constexpr int kExchangeFrontierMax = 64;
 // short-range walks: search radius per group (rg, or r_fixed for every group when rg is
