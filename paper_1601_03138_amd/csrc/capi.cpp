@@ -144,7 +144,7 @@ int enqueue_keys_sort(fdx_ctx *c) {
     mark(c, 1);
     bool alt = false;
     HIPCHK(c, radix_sort(n, c->key.p, c->key_alt.p, c->perm.p, c->perm_alt.p, c->sysid.p, S, 64,
-                         c->rs_scratch.p, c->partial.p, &alt, s,
+                         c->rs_scratch.p, &alt, s,
                          S > 1 && S <= 65536 && c->sys_carry.cap >= 2 * n ? c->sys_carry.p
                                                                            : nullptr));
     c->skey = alt ? c->key_alt.p : c->key.p;

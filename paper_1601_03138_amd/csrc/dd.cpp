@@ -236,7 +236,7 @@ int fdx_decompose(fdx_ctx *c, int32_t nx, int32_t ny, int32_t nz, int64_t n_samp
     for (const Level &L : levels) {
         bool alt = false;
         HIPCHK(c, radix_sort(K, kin, kother, vin, vother, L.nseg > 1 ? d->cell.p : nullptr,
-                             (int)L.nseg, 64, d->scratch.p, c->partial.p, &alt, s));
+                             (int)L.nseg, 64, d->scratch.p, &alt, s));
         if (alt) { std::swap(kin, kother); std::swap(vin, vother); }
         // sorted samples in (kin, vin); the next level's input goes to (kother, vother)
         HIPCHK(c, dd_cut((uint32_t)K, L.nseg, start_in, L.n, vin, L.coord, L.next, d->cell.p,
@@ -252,7 +252,7 @@ int fdx_decompose(fdx_ctx *c, int32_t nx, int32_t ny, int32_t nz, int64_t n_samp
                         d->pkey.p, d->pval.p, s));
     bool palt = false;
     HIPCHK(c, radix_sort(N, d->pkey.p, d->pkey_alt.p, d->pval.p, d->pval_alt.p, nullptr, 1,
-                         bits_for(D - 1), c->rs_scratch.p, c->partial.p, &palt, s));
+                         bits_for(D - 1), c->rs_scratch.p, &palt, s));
     d->order = palt ? d->pval_alt.p : d->pval.p;
     const uint64_t *psorted = palt ? d->pkey_alt.p : d->pkey.p;
     HIPCHK(c, hipMemsetAsync(d->run_lo.p, 0, 4 * D * nsrc, s));

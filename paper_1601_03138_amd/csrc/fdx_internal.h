@@ -112,7 +112,7 @@ size_t radix_scratch_u32(size_t n);
 // identity, and sysid be indexed by the original index).
 hipError_t radix_sort(size_t n, uint64_t *key, uint64_t *key_alt, uint32_t *val,
                       uint32_t *val_alt, const uint32_t *sysid, int nsys, int key_bits,
-                      uint32_t *scratch, uint64_t *partial, bool *result_in_alt, hipStream_t s,
+                      uint32_t *scratch, bool *result_in_alt, hipStream_t s,
                       uint16_t *carry = nullptr);
 
 // sorted particle data

@@ -154,9 +154,16 @@ int fdx_calc_force_noalloc(int device, void *hip_stream, int64_t n, const double
     cv.take(c.perm, N);
     cv.take(c.perm_alt, N);
     cv.take(c.inv, N);
-    cv.take(c.rs_scratch, radix_scratch_u32(std::max<size_t>(N, gcap)));
+    // (a size that leaves the lists the room they always had)
+    cv.take(c.rs_scratch, 512 * ((std::max<size_t>(N, gcap) + 2047) / 2048));
     cv.take(c.jp, N);
     cv.take(c.packed, N);
+    if (c.rs_scratch.cap < radix_scratch_u32(N)) {
+        // a few thousand particles more than one workgroup sorts: the sorted records' memory,
+        // which is written after the sort (more than 32 bytes per particle for at most 19 KiB)
+        c.rs_scratch.p = reinterpret_cast<uint32_t *>(c.jp.p);
+        c.rs_scratch.cap = 8 * N;
+    }
     cv.take(c.seps, N);
     cv.take(c.flag, N);
     cv.take(c.gcell_at, N);
