@@ -333,6 +333,8 @@ hipError_t far_expand(size_t gmax, const ForceArgs &a, hipStream_t s);
 // G = number of groups (direct launch: one workgroup per group; persistent launch: G bounds
 // the grid and the kernel reads the true count from the device status).
 hipError_t force(size_t G, const ForceArgs &a, hipStream_t s);
+// monopole forces with the S2 cutoff (a.r_cut), no potential
+hipError_t cut_force(size_t G, const ForceArgs &a, hipStream_t s);
 int force_variants();
 const char *force_variant_name(int v);
 int force_variant_capacity(int v);   // largest group one workgroup of variant v takes

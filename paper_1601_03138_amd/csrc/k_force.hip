@@ -28,6 +28,7 @@
 // Newton-Raphson step.
 #include "dev_util.h"
 #include "fdx_internal.h"
+#include "group_queue.h"
 #include "interact.h"
 
 namespace fdx {
@@ -48,7 +49,6 @@ struct KArgs {
     double4 *fs;
     DevStatus *st;
     uint32_t G;              // groups (direct launch); persistent kernels read *ngroups
-    double cut_s;            // cutoff kernel: 2 / r_cut
     const uint32_t *near;    // FP32 with a far-field expansion: near superparticles per group
                              // (kNone: not expanded), or null
 };
@@ -81,7 +81,7 @@ struct Smem {
     uint32_t slot;
 };
 
-template <class T, bool QUAD, int NT, int IPL, bool PF, bool CUT, int JT>
+template <class T, bool QUAD, int NT, int IPL, bool PF, int JT>
 __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T, NT, IPL, JT> &sm) {
     static_assert(JT <= NT && NT % JT == 0, "a tile holds at most one entry per thread");
     using V = typename V4<T>::t;
@@ -96,7 +96,7 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
     const uint32_t *spj = epj + capg - ns;
     // superparticles evaluated here: the first `near` of the group's when its far ones were
     // expanded (k_far.hip; their field is in fs), else all
-    constexpr bool FAR = sizeof(T) == 4 && !CUT;
+    constexpr bool FAR = sizeof(T) == 4;
     const uint32_t near = FAR && a.near ? uniform_u32(a.near[gi]) : kNone;
     const bool far = FAR && near != kNone;
     if (far) ns = near;
@@ -104,7 +104,6 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
     const double cx = fp32 ? uniform_f64(a.gcentre[3 * gi]) : 0.0;
     const double cy = fp32 ? uniform_f64(a.gcentre[3 * gi + 1]) : 0.0;
     const double cz = fp32 ? uniform_f64(a.gcentre[3 * gi + 2]) : 0.0;
-    const T cut_s = (T)a.cut_s;
 
     uint32_t tps = (ni + IPL - 1) / IPL;
     tps = tps < 1 ? 1 : (tps > (uint32_t)NT ? (uint32_t)NT : tps);
@@ -156,14 +155,14 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
                     const V J = run[q];
 #pragma unroll
                     for (int k = 0; k < IPL; k++)
-                        pp<T, CUT>(J, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k], cut_s);
+                        pp<T>(J, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k]);
                 }
                 const uint32_t j = kmain * nslice + slice;
                 if (j < nt) {
                     const V J = sm.e[j];
 #pragma unroll
                     for (int k = 0; k < IPL; k++)
-                        pp<T, CUT>(J, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k], cut_s);
+                        pp<T>(J, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k]);
                 }
 #pragma unroll
                 for (int k = 0; k < IPL; k++) {
@@ -215,8 +214,7 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
                     if (QUAD) { B = run[3 * q + 1]; C = run[3 * q + 2]; } else { B = A; C = A; }
 #pragma unroll
                     for (int k = 0; k < IPL; k++)
-                        pc<T, QUAD, CUT>(A, B, C, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k],
-                                         cut_s);
+                        pc<T, QUAD>(A, B, C, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k]);
                 }
                 const uint32_t j = kmain * nslice + slice;
                 if (j < nt) {
@@ -225,8 +223,7 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
                     if (QUAD) { B = sm.s[3 * j + 1]; C = sm.s[3 * j + 2]; } else { B = A; C = A; }
 #pragma unroll
                     for (int k = 0; k < IPL; k++)
-                        pc<T, QUAD, CUT>(A, B, C, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k],
-                                         cut_s);
+                        pc<T, QUAD>(A, B, C, xi[k], yi[k], zi[k], e2[k], tx[k], ty[k], tz[k], tp[k]);
                 }
 #pragma unroll
                 for (int k = 0; k < IPL; k++) {
@@ -246,7 +243,7 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
             // that hold a particle of the group read its mass (a slot past n_i does not)
             const uint32_t i = li + k * tps;
             double self = 0.0;
-            if (!CUT && slice == 0 && i < ni) self = (double)((T)a.jp[gb + i].w * rsqrt_t(e2[k]));
+            if (slice == 0 && i < ni) self = (double)((T)a.jp[gb + i].w * rsqrt_t(e2[k]));
             o[0] = ax[k].val(); o[1] = ay[k].val(); o[2] = az[k].val(); o[3] = self + ph[k].val();
         }
     }
@@ -266,13 +263,13 @@ __device__ __forceinline__ void force_group(const KArgs &a, uint32_t gi, Smem<T,
         const double *o = sm.red + 4 * ((size_t)k * NT + lk) + c;
 #pragma unroll 1
         for (uint32_t q = 0; q < nslice; q++) v += o[4 * (size_t)q * tps];
-        reinterpret_cast<double *>(a.fs + r)[c] = (CUT && c == 3) ? 0.0 : v;
+        reinterpret_cast<double *>(a.fs + r)[c] = v;
     }
     __syncthreads();
 }
 
 // OCC: minimum waves per SIMD the register allocation must allow (1 = no constraint).
-template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC, bool CUT, int JT>
+template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC, int JT>
 __global__ void __launch_bounds__(NT, OCC)
 k_force_direct(KArgs a) {
     __shared__ Smem<T, NT, IPL, JT> sm;
@@ -282,49 +279,26 @@ k_force_direct(KArgs a) {
     const uint32_t chunk = (G + 7) / 8;
     const uint32_t q = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
     if (q >= G) return;
-    force_group<T, QUAD, NT, IPL, PF, CUT, JT>(a, a.order ? a.order[q] : q, sm);
+    force_group<T, QUAD, NT, IPL, PF, JT>(a, a.order ? a.order[q] : q, sm);
 }
 
-// Persistent variant: a fixed grid pops work from device counters.  Without an explicit list
-// the groups are split into eight contiguous runs in tree order (at equal cumulative cost when
-// bounds are given, else of equal group counts), one queue per XCD
-// (consecutive workgroups are dispatched round-robin over the 8 XCDs, so workgroup b runs on
-// XCD b % 8); a workgroup pops from its own XCD's queue, keeping neighbouring groups -- which
-// share most of their lists -- in one L2, and once that queue is empty takes slots from the
-// other XCDs' queues, which balances the load.  With an explicit list (order + device count)
-// it pops one shared queue.
-template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC, bool CUT, int JT>
+// Persistent variant: a fixed grid pops work from device counters (group_queue.h).
+template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC, int JT>
 __global__ void __launch_bounds__(NT, OCC)
 k_force_persistent(KArgs a) {
     __shared__ Smem<T, NT, IPL, JT> sm;
     const uint32_t G = *a.ngroups;
-    const uint32_t x = blockIdx.x % 8u, chunk = (G + 7u) / 8u;
     for (;;) {
-        if (threadIdx.x == 0) {
-            uint32_t slot = kNone;
-            if (a.order) {
-                slot = atomicAdd(&a.st->queue_head, 1u);
-            } else {
-                for (uint32_t t = 0; t < 8u && slot == kNone; t++) {
-                    const uint32_t q = (x + t) & 7u;
-                    const uint32_t lo = a.bounds ? a.bounds[q] : q * chunk;
-                    const uint32_t hi = a.bounds ? a.bounds[q + 1] : min(G, lo + chunk);
-                    if (lo >= hi) continue;
-                    const uint32_t k = atomicAdd(&a.st->xcd_head[q], 1u);
-                    if (k < hi - lo) slot = lo + k;
-                }
-            }
-            sm.slot = slot;
-        }
+        if (threadIdx.x == 0) sm.slot = pop_group(a.st, G, a.bounds, a.order != nullptr);
         __syncthreads();
         const uint32_t slot = sm.slot;
         __syncthreads();
         if (slot >= G) break;
-        force_group<T, QUAD, NT, IPL, PF, CUT, JT>(a, a.order ? a.order[slot] : slot, sm);
+        force_group<T, QUAD, NT, IPL, PF, JT>(a, a.order ? a.order[slot] : slot, sm);
     }
 }
 
-template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC = 1, bool CUT = false, int JT = NT>
+template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC = 1, int JT = NT>
 hipError_t launch(const KArgs &k, bool persistent, hipStream_t s) {
     if (persistent) {
         int dev = 0, ncu = 256;
@@ -332,16 +306,16 @@ hipError_t launch(const KArgs &k, bool persistent, hipStream_t s) {
         (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
         int per_cu = 0;
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(k_force_persistent<T, QUAD, NT, IPL, PF, OCC, CUT, JT>), NT, 0);
+            &per_cu, reinterpret_cast<const void *>(k_force_persistent<T, QUAD, NT, IPL, PF, OCC, JT>), NT, 0);
         if (per_cu < 1) per_cu = 1;
         size_t grid = (size_t)ncu * per_cu;
         if (k.G && grid > k.G) grid = k.G;
-        hipLaunchKernelGGL((k_force_persistent<T, QUAD, NT, IPL, PF, OCC, CUT, JT>), dim3((unsigned)grid), dim3(NT),
+        hipLaunchKernelGGL((k_force_persistent<T, QUAD, NT, IPL, PF, OCC, JT>), dim3((unsigned)grid), dim3(NT),
                            0, s, k);
     } else {
         if (k.G == 0) return hipSuccess;
         const uint32_t chunk = (k.G + 7) / 8;
-        hipLaunchKernelGGL((k_force_direct<T, QUAD, NT, IPL, PF, OCC, CUT, JT>), dim3(8 * chunk), dim3(NT), 0, s, k);
+        hipLaunchKernelGGL((k_force_direct<T, QUAD, NT, IPL, PF, OCC, JT>), dim3(8 * chunk), dim3(NT), 0, s, k);
     }
     return hipGetLastError();
 }
@@ -374,10 +348,10 @@ hipError_t launch_v(const KArgs &k, bool persistent, int v, hipStream_t s) {
         case 7: return launch<T, QUAD, 512, 2, false>(k, persistent, s);
         case 8: return launch<T, QUAD, 512, 1, true, kW8<T>>(k, persistent, s);
         case 9: return launch<T, QUAD, 512, 1, false, kW8<T>>(k, persistent, s);
-        case 10: return launch<T, QUAD, 256, 1, false, 1, false, 64>(k, persistent, s);
-        case 11: return launch<T, QUAD, 256, 1, false, 1, false, 128>(k, persistent, s);
-        case 12: return launch<T, QUAD, 512, 1, false, kW8<T>, false, 128>(k, persistent, s);
-        default: return launch<T, QUAD, 512, 1, false, kW8<T>, false, 256>(k, persistent, s);
+        case 10: return launch<T, QUAD, 256, 1, false, 1, 64>(k, persistent, s);
+        case 11: return launch<T, QUAD, 256, 1, false, 1, 128>(k, persistent, s);
+        case 12: return launch<T, QUAD, 512, 1, false, kW8<T>, 128>(k, persistent, s);
+        default: return launch<T, QUAD, 512, 1, false, kW8<T>, 256>(k, persistent, s);
     }
 }
 
@@ -386,8 +360,8 @@ template <class T, bool QUAD, int NT, int IPL, bool PF, int OCC = 1, int JT = NT
 int scratch_of(bool persistent) {
     hipFuncAttributes at{};
     const void *f = persistent
-        ? reinterpret_cast<const void *>(k_force_persistent<T, QUAD, NT, IPL, PF, OCC, false, JT>)
-        : reinterpret_cast<const void *>(k_force_direct<T, QUAD, NT, IPL, PF, OCC, false, JT>);
+        ? reinterpret_cast<const void *>(k_force_persistent<T, QUAD, NT, IPL, PF, OCC, JT>)
+        : reinterpret_cast<const void *>(k_force_direct<T, QUAD, NT, IPL, PF, OCC, JT>);
     if (hipFuncGetAttributes(&at, f) != hipSuccess) return -1;
     return (int)at.localSizeBytes;
 }
@@ -430,6 +404,7 @@ int force_variant_capacity(int v) {
 }
 
 hipError_t force(size_t G, const ForceArgs &fa, hipStream_t s) {
+    if (fa.r_cut > 0) return cut_force(G, fa, s);          // tree part of TreePM
     KArgs k;
     k.gbegin = fa.g->begin; k.gcount = fa.g->count; k.gcentre = fa.g->centre;
     k.jp = fa.jp; k.seps = fa.seps; k.mom = fa.mom;
@@ -439,14 +414,7 @@ hipError_t force(size_t G, const ForceArgs &fa, hipStream_t s) {
     k.ngroups = fa.count ? fa.count : &fa.st->n_groups_c;
     k.fs = fa.fs; k.st = fa.st;
     k.G = (uint32_t)G;
-    k.cut_s = fa.r_cut > 0 ? 2.0 / fa.r_cut : 0.0;
     k.near = fa.near;
-    if (fa.r_cut > 0) {                // tree part of TreePM: monopole with the S2 cutoff
-        if (!fa.fp32) return launch<double, false, 256, 2, false, 1, true>(k, fa.persistent, s);
-        // the persistent loop holds the 64-register budget only without the register prefetch
-        return fa.persistent ? launch<float, false, 512, 1, false, 8, true>(k, true, s)
-                             : launch<float, false, 512, 1, true, 8, true>(k, false, s);
-    }
     const int v = fa.variant;
     if (fa.fp32) return fa.quad ? launch_v<float, true>(k, fa.persistent, v, s)
                                 : launch_v<float, false>(k, fa.persistent, v, s);
