@@ -243,6 +243,19 @@ __device__ __forceinline__ void wave_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Order of blocks of neighbouring groups over the 8 XCDs: blocks go to the XCDs in turn, and the
+// blocks of one XCD take runs of kXcdRun consecutive blocks of groups, so groups near each other,
+// whose lists overlap, are worked on behind one L2, while every XCD still gets dense and sparse
+// regions.  Grids are multiples of 8 kXcdRun, or the whole of it.
+constexpr uint32_t kXcdRun = 64;
+__host__ __device__ inline uint32_t xcd_run_blocks(size_t blocks) {
+    return (uint32_t)((blocks + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun));
+}
+__device__ __forceinline__ uint32_t xcd_run_block(uint32_t vb) {
+    const uint32_t nb = vb / 8u;
+    return (nb / kXcdRun * 8u + vb % 8u) * kXcdRun + nb % kXcdRun;
+}
+
 // Grid-stride index helpers.
 __device__ __forceinline__ size_t gtid() { return (size_t)blockIdx.x * blockDim.x + threadIdx.x; }
 __device__ __forceinline__ size_t gstride() { return (size_t)gridDim.x * blockDim.x; }

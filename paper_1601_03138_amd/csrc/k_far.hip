@@ -27,7 +27,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kScan = 2;                          // list entries per lane and block
 constexpr uint32_t kBlock = kScan * kWave;        // entries read together
-constexpr uint32_t kRunB = 64;                    // blocks of groups an XCD takes in a row
 constexpr uint32_t kQueue = kBlock + kWave;       // a block on top of a part-filled round
 constexpr uint32_t kHeld = 4 * kBlock;            // ids waiting for a free slot, per kind
 
@@ -211,17 +210,11 @@ k_far(FarArgs a) {
     const uint64_t lt = lanemask_lt();
     const uint32_t G = min(*a.ngroups, a.gmax);
     const double2 *mom = reinterpret_cast<const double2 *>(a.mom);
-    // Blocks go to the 8 XCDs in turn (the grid is a multiple of 8 kRunB).  The blocks of one XCD
-    // take runs of kRunB consecutive blocks of groups, so groups near each other, which share
-    // most of their superparticles, are expanded behind one L2, while every XCD still gets dense
-    // and sparse regions.  The four waves of a block take four consecutive groups, whose lists
-    // begin with the same cells of the upper tree.
-    const uint32_t round = 8 * kRunB;
-    const uint32_t vblocks = ((G + kWaves - 1) / kWaves + round - 1) / round * round;
+    // The four waves of a block take four consecutive groups, whose lists begin with the same
+    // cells of the upper tree; blocks of neighbouring groups share an XCD.
+    const uint32_t vblocks = xcd_run_blocks((G + kWaves - 1) / kWaves);
     for (uint32_t vb = blockIdx.x; vb < vblocks; vb += gridDim.x) {
-    const uint32_t nb = vb / 8u;
-    const uint32_t blk = (nb / kRunB * 8u + vb % 8u) * kRunB + nb % kRunB;
-    const uint32_t gi = uniform_u32(blk * kWaves + (uint32_t)w);
+    const uint32_t gi = uniform_u32(xcd_run_block(vb) * kWaves + (uint32_t)w);
     if (gi >= G) continue;
     const FarGeom f = a.geom[gi];
     const uint32_t ns = uniform_u32(a.cnt_s[gi]), ni = uniform_u32(a.gcount[gi]);
@@ -383,9 +376,8 @@ k_far(FarArgs a) {
 
 hipError_t far_expand(size_t gmax, const ForceArgs &fa, hipStream_t s) {
     if (!gmax) return hipSuccess;
-    const size_t round = 8 * kRunB;
-    const size_t blocks = ((gmax + kWaves - 1) / kWaves + round - 1) / round * round;
-    const unsigned grid = (unsigned)std::min<size_t>(blocks, 32 * round);
+    const size_t blocks = xcd_run_blocks((gmax + kWaves - 1) / kWaves);
+    const unsigned grid = (unsigned)std::min<size_t>(blocks, 256 * kXcdRun);
     FarArgs a;
     a.ngroups = &fa.st->n_groups_c;
     a.gcount = fa.g->count; a.geom = fa.g->far; a.mom = fa.mom;
