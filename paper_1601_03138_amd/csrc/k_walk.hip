@@ -22,6 +22,8 @@
 #include "opening.h"
 #include "walk_order.h"
 
+#include <algorithm>
+
 namespace fdx {
 
 namespace {
@@ -242,6 +244,11 @@ k_walk(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *link, 
 constexpr int kRun = 4;                 // groups per run
 static_assert(kWaves == (int)kWalkOrderWaves, "walk_order.h assumes the walk's waves per block");
 constexpr int kFront = 224;             // frontier cells kept per wave
+// Up to this many groups (two waves for each that the chip holds) every group has a wave, which
+// repeats its run's first walk; beyond, a run has one.  Latency bound when few: a walk is a
+// serial chain of stack pops.  Fill walk, a wave per run / per group: 298 groups (4096 particles)
+// 77 / 34 us, 1500 groups 88 / 36 us, 14210 groups 252 / 210 us, 83047 groups 575 / 770 us.
+constexpr uint32_t kSplitGroups = 16384;
 
 // the opening test at the box's far corners: false means every box inside [bmin, bmax] opens
 // the cell (per axis max(c - bmin, bmax - c) bounds the distance to any box inside; the
@@ -369,7 +376,7 @@ __device__ __forceinline__ void group_box(const Groups &g, uint32_t gi, int (&b)
     }
 }
 
-// One wave per run (or per selected group).  Arguments as k_walk's (gravity).  Held to 8
+// One wave per run (or per group: kSplitGroups, a selection).  Arguments as k_walk's (gravity).  Held to 8
 // waves per SIMD (the limit that the LDS of 8 workgroups per CU also sets); the bound makes
 // the compiler keep some scalar values in vector lanes, and without it the kernel ran at 7
 // waves per SIMD and was slower.
@@ -389,7 +396,8 @@ k_walk_runs(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *l
     uint32_t *stk = stack_all[w];
     uint32_t *front = front_all[w];
     const uint32_t G = min(*ngroups, g.cap);
-    const uint32_t items = sel ? *nsel : (G + kRun - 1) / kRun;
+    const bool each = sel != nullptr || G <= kSplitGroups;
+    const uint32_t items = sel ? *nsel : each ? G : (G + kRun - 1) / kRun;
     // this wave's slot within each W: a permutation of 0..W-1
     const uint32_t slot = walk_order_slot(blockIdx.x, (uint32_t)w, gridDim.x, sel ? 0u : chunk);
     // the two arguments the stack loops read: apart from the argument tuples, so that the
@@ -399,9 +407,9 @@ k_walk_runs(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *l
     uint32_t *const lst = own_sgpr_pair(list);
     for (size_t q = slot; q < items; q += (size_t)gridDim.x * kWaves) {
         // targets [t0, t1) of run [r0, r1)
-        const uint32_t t0 = uniform_u32(sel ? sel[q] : (uint32_t)q * kRun);
+        const uint32_t t0 = uniform_u32(sel ? sel[q] : each ? (uint32_t)q : (uint32_t)q * kRun);
         if (t0 >= G) continue;
-        const uint32_t t1 = sel ? t0 + 1 : min(t0 + kRun, G);
+        const uint32_t t1 = each ? t0 + 1 : min(t0 + kRun, G);
         const uint32_t r0 = t0 / kRun * kRun, r1 = min(r0 + kRun, G);
         const int nt = (int)(t1 - t0);
         const uint32_t root = g.sys[r0];                  // roots are cells 0..nsys-1
@@ -810,7 +818,8 @@ hipError_t walk_runs(bool fill, size_t gmax, const Groups g, const Cells c, doub
                      uint64_t *seg, uint32_t *cap, uint64_t list_cap, uint32_t *list,
                      uint32_t *cnt_e, uint32_t *cnt_s, uint32_t *ovf_list, const uint32_t *sel,
                      const uint32_t *nsel, DevStatus *st, hipStream_t s, bool spill) {
-    const size_t items = sel ? gmax : (gmax + kRun - 1) / kRun;
+    const size_t items = sel ? gmax : std::max(std::min(gmax, (size_t)kSplitGroups),
+                                               (gmax + kRun - 1) / kRun);
     size_t grid = grid_waves(items);
     uint32_t chunk = 0;
     if (!sel) walk_order_launch(items, grid, &grid, &chunk);
