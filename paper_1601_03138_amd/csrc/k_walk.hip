@@ -49,6 +49,15 @@ __device__ __forceinline__ bool cell_far(const uint4 nd, int bminx, int bminy, i
     return D2 > R2;
 }
 
+// How many of lc entries from slot e0 on fit a segment of capg.  The difference is kept apart from
+// the comparison: the compiler (clang 22, ROCm 7.2) otherwise drops the comparison, takes the
+// difference as non-negative, and a list that has outgrown its segment runs on behind it.
+__device__ __forceinline__ uint32_t fitting(uint32_t lc, uint32_t e0, uint32_t capg) {
+    uint32_t room = capg - e0;
+    asm("" : "+v"(room));
+    return e0 < capg ? min(lc, room) : 0u;
+}
+
 // KIND 0: gravity (opening angle; accepted cells are superparticles).  Short range, search
 // radius r: 1 the group's radius (fixed cutoff or the group's largest h), 2 the cell's largest
 // h (scatter), 3 the larger of the two (symmetric).  4: tree part of TreePM, cells beyond the
@@ -159,7 +168,7 @@ k_walk(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *link, 
             // exec mask and the scalar unit out of the chunk
             if (FILL && leaf) {
                 const uint32_t e0 = ne + lex;
-                const uint32_t nw = e0 < capg ? min(lc, capg - e0) : 0u;
+                const uint32_t nw = fitting(lc, e0, capg);
                 uint32_t *dst = list + base + e0;
                 // unconditional stores: slots past nw rewrite slot nw - 1 with its own value
                 for (uint32_t k0 = 0; k0 < nw; k0 += 8) {
@@ -338,7 +347,7 @@ __device__ __forceinline__ int run_stack(uint32_t *stk, uint32_t sp, uint32_t *f
 #pragma unroll
             for (int k = 0; k < NT; k++) {
                 if (k >= nt) continue;
-                const uint32_t nw = e0 < capg[k] ? min(lc, capg[k] - e0) : 0u;
+                const uint32_t nw = fitting(lc, e0, capg[k]);
                 uint32_t *dst = list + base[k] + e0;
                 // unconditional stores: slots past nw rewrite slot nw - 1 with its own value
                 for (uint32_t k0 = 0; k0 < nw; k0 += 8) {
