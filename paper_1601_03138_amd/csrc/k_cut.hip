@@ -47,7 +47,8 @@ struct CutArgs {
 // to the cutoff, and 0 from there on.
 template <class T>
 __device__ __forceinline__ T s2_cutoff(T xi) {
-    const T u = max((T)2 - xi, (T)0), u2 = u * u, u5 = u2 * u2 * u;
+    xi = min(xi, (T)2);
+    const T u = (T)2 - xi, u2 = u * u, u5 = u2 * u2 * u;
     const T s = max((T)1 - xi, (T)0), s2 = s * s, s6 = s2 * s2 * s2;
     T p = fma(xi, (T)0.05, (T)(22.0 / 140.0));
     p = fma(xi, p, (T)(10.0 / 140.0));
