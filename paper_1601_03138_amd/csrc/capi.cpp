@@ -164,7 +164,7 @@ int enqueue_tree_groups(fdx_ctx *c) {
     HIPCHK(c, tree_build(n, S, c->sys_off.p, c->skey, c->n_leaf, cells_view(c),
                          (uint8_t *)c->tmp_n.p, c->tmp_off.p, c->partial.p, c->st, s));
     mark(c, 3);
-    HIPCHK(c, tree_moments(cells_view(c), c->jp.p, s));
+    HIPCHK(c, tree_moments(n, S, c->sys_off.p, c->tmp_off.p, cells_view(c), c->jp.p, s));
     mark(c, 4);
     HIPCHK(c, make_groups(n, S, c->sys_off.p, cells_view(c), c->skey, c->cube.p, c->seps.p,
                           c->n_group, groups_view(c), c->flag.p, c->gcell_at.p, c->gpos.p,

@@ -124,13 +124,20 @@ hipError_t gather_sorted(size_t n, const uint32_t *perm, const double4 *packed,
                          const double *eps, double eps_all, bool per_system, const int64_t *off,
                          int nsys, double4 *jp, double *seps, uint32_t *inv, hipStream_t s);
 
-// tree
+// tree: the build counts cells per tile of kTileW sorted positions (a wave's share) and level
+// Rounds of 64 positions per tile, one after another: with 16 the counting and the writing of the
+// cells took 24 us each at any size below 10^6 particles; with 4, 8 and 9 us at 21k, 10 and 11 us
+// at 2^20, 90 and 119 us at 2^24 (16: 95 and 148; 2: 96 and 138).
+constexpr int kTileRounds = 4;
+constexpr int kTileW = kTileRounds * 64;
 // scratch words tree_build needs besides 3 n bytes
 size_t tree_scratch_u32(size_t n);
 hipError_t tree_build(size_t n, int nsys, const int64_t *sys_off, const uint64_t *skey,
                       int n_leaf, Cells c, uint8_t *bytes, uint32_t *scratch,
                       uint64_t *partial, DevStatus *st, hipStream_t s);
-hipError_t tree_moments(Cells c, const double4 *jp, hipStream_t s);
+// moments of all cells; scratch as tree_build left it
+hipError_t tree_moments(size_t n, int nsys, const int64_t *sys_off, const uint32_t *scratch, Cells c,
+                        const double4 *jp, hipStream_t s);
 // groups, their boxes and centres, and the wide flag: with d = depth of the group's deepest
 // leaf below its cell, S the cell side and eps_min the smallest softening among its members,
 // a group is wide iff 9 u min(S / eps_min, 2^d) > 1e-4 (u = 2^-24), i.e. FP32 rounding of
@@ -207,7 +214,8 @@ hipError_t walk_short(bool fill, int kind, size_t gmax, const Groups g, const Ce
 // 1 scatter, 2 gather, 3 symmetric), and their return to the caller's order
 hipError_t sph_radius(size_t n, const uint32_t *perm, const double *h, double r_fixed,
                       double *sh, DevStatus *st, hipStream_t s);
-hipError_t sph_cell_hmax(const Cells c, const double *sh, double *hmax, hipStream_t s);
+hipError_t sph_cell_hmax(size_t n, int nsys, const int64_t *sys_off, const uint32_t *scratch,
+                         const Cells c, const double *sh, double *hmax, hipStream_t s);
 hipError_t sph_group_hmax(size_t gmax, const Groups g, const double *sh, double *rg,
                           DevStatus *st, hipStream_t s);
 hipError_t sph_density(int mode, size_t gmax, const Groups g, const uint64_t *seg,

@@ -14,6 +14,7 @@
 // |r_ij|^2 = dx*dx + dy*dy + dz*dz is rounded as written (no contraction) and compared with
 // H*H, so which pairs count is exact.  FP64 throughout; one workgroup per group, candidate
 // tiles staged in LDS, per-slice partial sums combined in slice order (deterministic).
+#include "bottom_up.h"
 #include "dev_util.h"
 #include "fdx_internal.h"
 #include "sift.h"
@@ -42,22 +43,21 @@ __global__ void k_sph_radius(size_t n, const uint32_t *perm, const double *h, do
     }
 }
 
-// largest support radius in every cell of level l (children done first)
-__global__ void k_cell_hmax(int l, Cells c, const double *sh, double *hmax) {
-    const uint32_t c0 = c.lvl[l], c1 = c.lvl[l + 1];
-    for (size_t k = gtid(); k < c1 - c0; k += gstride()) {
-        const uint32_t cid = c0 + (uint32_t)k;
-        double v = 0.0;
-        const uint32_t nch = c.nchild[cid];
-        if (nch == 0) {
-            const uint32_t b = c.begin[cid], e = b + c.count[cid];
-            for (uint32_t i = b; i < e; i++) v = fmax(v, sh[i]);
-        } else {
-            const uint32_t f = c.first[cid];
-            for (uint32_t j = f; j < f + nch; j++) v = fmax(v, hmax[j]);
-        }
-        hmax[cid] = v;
-    }
+// largest support radius in every cell, from the leaves up (bottom_up.h)
+__device__ __forceinline__ void cell_hmax(const double *sh, double *hmax, const UpCell &u) {
+    double v = 0.0;
+    const double *p = u.nch ? hmax : sh;
+    const uint32_t e = u.first + (u.nch ? u.nch : u.count);
+    for (uint32_t i = u.first; i < e; i++) v = fmax(v, p[i]);
+    hmax[u.id] = v;
+}
+__global__ void __launch_bounds__(kUpThreads)
+k_cell_hmax(Cells c, const double *sh, double *hmax, UpBlocks u) {
+    up_inside(c, u, [&](const UpCell &k) { cell_hmax(sh, hmax, k); });
+}
+__global__ void __launch_bounds__(kUpThreads)
+k_cell_hmax_across(Cells c, const double *sh, double *hmax, UpBlocks u, uint32_t fan) {
+    up_across(c, u, fan, [&](const UpCell &k) { cell_hmax(sh, hmax, k); });
 }
 
 // largest support radius of every group (one wave per group)
@@ -270,10 +270,16 @@ hipError_t sph_radius(size_t n, const uint32_t *perm, const double *h, double r_
     return hipGetLastError();
 }
 
-hipError_t sph_cell_hmax(const Cells c, const double *sh, double *hmax, hipStream_t s) {
-    const unsigned grid = grid_for(c.cap, 4096);
-    for (int l = kLevels; l >= 0; l--)
-        hipLaunchKernelGGL(k_cell_hmax, dim3(grid), dim3(kThreads), 0, s, l, c, sh, hmax);
+hipError_t sph_cell_hmax(size_t n, int nsys, const int64_t *sys_off, const uint32_t *scratch,
+                         const Cells c, const double *sh, double *hmax, hipStream_t s) {
+    up_launch(up_blocks(n, nsys, sys_off, scratch),
+              [&](uint32_t grid, int threads, const UpBlocks &u) {
+                  hipLaunchKernelGGL(k_cell_hmax, dim3(grid), dim3(threads), 0, s, c, sh, hmax, u);
+              },
+              [&](uint32_t grid, int threads, const UpBlocks &u, uint32_t fan) {
+                  hipLaunchKernelGGL(k_cell_hmax_across, dim3(grid), dim3(threads), 0, s, c, sh,
+                                     hmax, u, fan);
+              });
     return hipGetLastError();
 }
 

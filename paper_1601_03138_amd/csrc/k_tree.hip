@@ -13,6 +13,7 @@
 //
 // Groups (modified tree algorithm, section "Tree traverse and interaction calculation"):
 // maximal cells of at most n_group particles; an over-full leaf is cut into runs of n_group.
+#include "bottom_up.h"
 #include "dev_util.h"
 #include "far_field.h"
 #include "fdx_internal.h"
@@ -93,9 +94,6 @@ __global__ void k_tree_init(int nsys, const int64_t *off, Cells c, DevStatus *st
 // Breadth-first numbering (level by level, by position within a level) comes from one
 // exclusive scan over per-wave-tile cell counts laid out level-major.
 // ---------------------------------------------------------------------------------------
-
-constexpr int kTileRounds = 16;                    // rounds of 64 positions per wave tile
-constexpr int kTileW = kTileRounds * kWave;        // 1024 positions per wave tile
 
 __device__ __forceinline__ int shared_levels(uint64_t a, uint64_t b) {
     const uint64_t x = a ^ b;                       // keys use the low 63 bits
@@ -279,84 +277,99 @@ __global__ void k_cells_finish(int nsys, const int64_t *off, const uint64_t *ske
 //   M = sum m,  s = sum m r,  T = sum m r r^T (+ the children's own Q),  r = x - ref;
 //   X = ref + s / M,  A = T - M d d^T with d = s / M,  Q = 3 A - tr(A) I (traceless, about X).
 // A massless cell gets X = 0 and Q = 0.
-__device__ void cell_moments(const Cells &c, const double4 *jp, uint32_t cid) {
+struct CellSum {
     double M = 0, sx = 0, sy = 0, sz = 0;
     double txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
     double q[6] = {0, 0, 0, 0, 0, 0};
     double rx = 0, ry = 0, rz = 0;
-    const uint32_t nch = c.nchild[cid];
-    auto add = [&](double m, double x, double y, double z) {
+    __device__ __forceinline__ void add(double m, double x, double y, double z) {
         const double dx = x - rx, dy = y - ry, dz = z - rz;
         const double mx = m * dx, my = m * dy, mz = m * dz;
         M += m; sx += mx; sy += my; sz += mz;
         txx += mx * dx; tyy += my * dy; tzz += mz * dz;
         txy += mx * dy; txz += mx * dz; tyz += my * dz;
-    };
-    if (nch == 0) {
-        const uint32_t b = c.begin[cid], e = b + c.count[cid];
+    }
+    __device__ __forceinline__ void store(double *mom, uint32_t cid) {
+        double X = 0, Y = 0, Z = 0;
+        if (M > 0) {
+            const double dx = sx / M, dy = sy / M, dz = sz / M;
+            X = rx + dx; Y = ry + dy; Z = rz + dz;
+            const double axx = txx - sx * dx, ayy = tyy - sy * dy, azz = tzz - sz * dz;
+            const double axy = txy - sx * dy, axz = txz - sx * dz, ayz = tyz - sy * dz;
+            const double tr = axx + ayy + azz;
+            q[0] += 3.0 * axx - tr; q[1] += 3.0 * ayy - tr; q[2] += 3.0 * azz - tr;
+            q[3] += 3.0 * axy; q[4] += 3.0 * axz; q[5] += 3.0 * ayz;
+        }
+        double2 *o = reinterpret_cast<double2 *>(mom + 10 * (size_t)cid);
+        o[0] = make_double2(M, X);
+        o[1] = make_double2(Y, Z);
+        o[2] = make_double2(q[0], q[1]);
+        o[3] = make_double2(q[2], q[3]);
+        o[4] = make_double2(q[4], q[5]);
+    }
+};
+
+constexpr int kLeafChunk = 4;
+// all leaves (most cells), apart from the levels above them: all of them at once.  Bound by the
+// latency of a few loads below 10^6 particles, by the scattered 80-byte records beyond (2^24
+// particles 355 us for about 1 GB; loads of whole chunks of 8, in range but unused: 412 us).
+__global__ void __launch_bounds__(kThreads)
+k_moments_leaves(Cells c, const double4 *jp) {
+    const uint32_t nc = c.lvl[kLevels + 1];
+    for (size_t k = gtid(); k < nc; k += gstride()) {
+        if (c.node[k].w >> 8) continue;
+        const uint2 lk = c.link[k];
+        const uint32_t b = lk.x, e = b + lk.y;
+        CellSum s;
         if (e > b) {
             const double4 p0 = jp[b];
-            rx = p0.x; ry = p0.y; rz = p0.z;
+            s.rx = p0.x; s.ry = p0.y; s.rz = p0.z;
         }
-        // chunks of 8 with every load of a chunk issued before its sums (leaves hold at most
-        // n_leaf particles, except at the deepest level)
-        for (uint32_t i0 = b; i0 < e; i0 += 8) {
-            double4 p[8];
+        // chunks with every load of a chunk issued before its sums
+        for (uint32_t i0 = b; i0 < e; i0 += kLeafChunk) {
+            double4 p[kLeafChunk];
 #pragma unroll
-            for (int k = 0; k < 8; k++) p[k] = jp[i0 + k < e ? i0 + k : b];   // in range
+                for (int j = 0; j < kLeafChunk; j++)
+                if (i0 + j < e) p[j] = jp[i0 + j];
 #pragma unroll
-            for (int k = 0; k < 8; k++)
-                if (i0 + k < e) add(p[k].w, p[k].x, p[k].y, p[k].z);
+            for (int j = 0; j < kLeafChunk; j++)
+                if (i0 + j < e) s.add(p[j].w, p[j].x, p[j].y, p[j].z);
         }
-    } else {
-        const uint32_t f = c.first[cid];
-        const double2 *m0 = reinterpret_cast<const double2 *>(c.mom + 10 * (size_t)f);
-        const double2 x01 = m0[0], x23 = m0[1];
-        rx = x01.y; ry = x23.x; rz = x23.y;
-        // at most 8 children: their records are loaded together, then summed in order
-        double2 a[8], bb[8];
+        s.store(c.mom, (uint32_t)k);
+    }
+}
+
+// an internal cell from its children, four at a time, every load of the four issued before its
+// sums
+__device__ __forceinline__ void inner_moments(const Cells &c, const UpCell &u) {
+    if (!u.nch) return;
+    CellSum s;
+    const double2 *m0 = reinterpret_cast<const double2 *>(c.mom + 10 * (size_t)u.first);
+    for (uint32_t k0 = 0; k0 < u.nch; k0 += 4) {
+        double2 o[4][5];
 #pragma unroll
-        for (uint32_t k = 0; k < 8; k++) {
-            const uint32_t j = k < nch ? f + k : f;                          // in range
-            const double2 *o = reinterpret_cast<const double2 *>(c.mom + 10 * (size_t)j);
-            a[k] = o[0];
-            bb[k] = o[1];
-        }
+        for (uint32_t k = 0; k < 4; k++)
 #pragma unroll
-        for (uint32_t k = 0; k < 8; k++)
-            if (k < nch) add(a[k].x, a[k].y, bb[k].x, bb[k].y);
+            for (uint32_t w = 0; w < 5; w++) o[k][w] = m0[5 * (k0 + k < u.nch ? k0 + k : k0) + w];
+        if (k0 == 0) { s.rx = o[0][0].y; s.ry = o[0][1].x; s.rz = o[0][1].y; }
 #pragma unroll
-        for (uint32_t k = 0; k < 8; k++) {
-            if (k < nch) {
-                const double2 *o = reinterpret_cast<const double2 *>(c.mom + 10 * (size_t)(f + k));
-                const double2 cq = o[2], dq = o[3], eq = o[4];
-                q[0] += cq.x; q[1] += cq.y; q[2] += dq.x; q[3] += dq.y; q[4] += eq.x;
-                q[5] += eq.y;
+        for (uint32_t k = 0; k < 4; k++) {
+            if (k0 + k < u.nch) {
+                s.add(o[k][0].x, o[k][0].y, o[k][1].x, o[k][1].y);
+                s.q[0] += o[k][2].x; s.q[1] += o[k][2].y; s.q[2] += o[k][3].x;
+                s.q[3] += o[k][3].y; s.q[4] += o[k][4].x; s.q[5] += o[k][4].y;
             }
         }
     }
-    double X = 0, Y = 0, Z = 0;
-    if (M > 0) {
-        const double dx = sx / M, dy = sy / M, dz = sz / M;
-        X = rx + dx; Y = ry + dy; Z = rz + dz;
-        const double axx = txx - sx * dx, ayy = tyy - sy * dy, azz = tzz - sz * dz;
-        const double axy = txy - sx * dy, axz = txz - sx * dz, ayz = tyz - sy * dz;
-        const double tr = axx + ayy + azz;
-        q[0] += 3.0 * axx - tr; q[1] += 3.0 * ayy - tr; q[2] += 3.0 * azz - tr;
-        q[3] += 3.0 * axy; q[4] += 3.0 * axz; q[5] += 3.0 * ayz;
-    }
-    double2 *o = reinterpret_cast<double2 *>(c.mom + 10 * (size_t)cid);
-    o[0] = make_double2(M, X);
-    o[1] = make_double2(Y, Z);
-    o[2] = make_double2(q[0], q[1]);
-    o[3] = make_double2(q[2], q[3]);
-    o[4] = make_double2(q[4], q[5]);
+    s.store(c.mom, u.id);
 }
-
-// moments of the cells of one level (children already done)
-__global__ void k_moments(int l, Cells c, const double4 *jp) {
-    const uint32_t c0 = c.lvl[l], c1 = c.lvl[l + 1];
-    for (size_t k = gtid(); k < c1 - c0; k += gstride()) cell_moments(c, jp, c0 + (uint32_t)k);
+// moments of the internal cells, from the deepest up (bottom_up.h)
+__global__ void __launch_bounds__(kUpThreads) k_moments(Cells c, UpBlocks u) {
+    up_inside(c, u, [&](const UpCell &k) { inner_moments(c, k); });
+}
+__global__ void __launch_bounds__(kUpThreads) k_moments_across(Cells c, UpBlocks u,
+                                                               uint32_t fan) {
+    up_across(c, u, fan, [&](const UpCell &k) { inner_moments(c, k); });
 }
 
 // Mark the first particle of every group: flag[r] = 1, gcell_at[r] = its cell.
@@ -547,10 +560,16 @@ hipError_t tree_build(size_t n, int nsys, const int64_t *sys_off, const uint64_t
     return hipGetLastError();
 }
 
-hipError_t tree_moments(Cells c, const double4 *jp, hipStream_t s) {
-    const unsigned grid = grid_for(c.cap, 4096);
-    for (int l = kLevels; l >= 0; l--)
-        hipLaunchKernelGGL(k_moments, dim3(grid), dim3(kThreads), 0, s, l, c, jp);
+hipError_t tree_moments(size_t n, int nsys, const int64_t *sys_off, const uint32_t *scratch, Cells c,
+                        const double4 *jp, hipStream_t s) {
+    hipLaunchKernelGGL(k_moments_leaves, dim3(grid_for(c.cap)), dim3(kThreads), 0, s, c, jp);
+    up_launch(up_blocks(n, nsys, sys_off, scratch),
+              [&](uint32_t grid, int threads, const UpBlocks &u) {
+                  hipLaunchKernelGGL(k_moments, dim3(grid), dim3(threads), 0, s, c, u);
+              },
+              [&](uint32_t grid, int threads, const UpBlocks &u, uint32_t fan) {
+                  hipLaunchKernelGGL(k_moments_across, dim3(grid), dim3(threads), 0, s, c, u, fan);
+              });
     return hipGetLastError();
 }
 
@@ -567,7 +586,7 @@ hipError_t make_groups(size_t n, int nsys, const int64_t *sys_off, Cells c,
     hipLaunchKernelGGL(k_group_emit, dim3(grid_for(n)), dim3(kThreads), 0, s, n, n_group, c, flag,
                        gcell_at, gpos, g);
     hipLaunchKernelGGL(k_leaf_level, dim3(grid_for(c.cap, 8192)), dim3(kThreads), 0, s, c, plev);
-    hipLaunchKernelGGL(k_group_geom, dim3(grid_for(n / 16 + 64, 4096)), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(k_group_geom, dim3(grid_for(16 * (size_t)g.cap, 4096)), dim3(kThreads), 0, s,
                        &st->n_groups, nsys, sys_off, c, skey, cube, seps, plev, g, st);
     return hipGetLastError();
 }

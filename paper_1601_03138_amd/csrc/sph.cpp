@@ -88,7 +88,8 @@ int fdx_calc_density(fdx_ctx *c, int32_t mode, double r_cut, const double *h, in
     const Groups gv = groups_view(c);
     if (mode == FDX_CUT_SCATTER || mode == FDX_CUT_SYMMETRIC) {
         HIPCHK(c, x->hmax.ensure(c->cell_cap));
-        HIPCHK(c, sph_cell_hmax(cv, x->sh.p, x->hmax.p, s));
+        HIPCHK(c, sph_cell_hmax(n, c->nsys, c->sys_off.p, c->tmp_off.p, cv, x->sh.p,
+                                x->hmax.p, s));
         sa.hmax = x->hmax.p;
     }
     if (mode == FDX_CUT_GATHER || mode == FDX_CUT_SYMMETRIC) {
