@@ -288,8 +288,11 @@ __global__ void __launch_bounds__(NT, OCC)
 k_force_persistent(KArgs a) {
     __shared__ Smem<T, NT, IPL, JT> sm;
     const uint32_t G = *a.ngroups;
-    for (;;) {
-        if (threadIdx.x == 0) sm.slot = pop_group(a.st, G, a.bounds, a.order != nullptr);
+    for (bool first = true;; first = false) {
+        if (threadIdx.x < kWave) {
+            const uint32_t k = pop_group<1>(a.st, G, a.bounds, a.order != nullptr, first, 0);
+            if (threadIdx.x == 0) sm.slot = k;
+        }
         __syncthreads();
         const uint32_t slot = sm.slot;
         __syncthreads();
