@@ -57,7 +57,6 @@ int ensure_tree_buffers(fdx_ctx *c, uint32_t cell_cap, uint32_t group_cap) {
         HIPCHK(c, c->c_mom.ensure(10 * (size_t)cell_cap));
         c->cell_cap = cell_cap;
     }
-    HIPCHK(c, c->c_lvl.ensure(kLevels + 2));
     HIPCHK(c, c->f_bounds.ensure(9));
     HIPCHK(c, c->tmp_n.ensure(n + S + 1));                 // >= 3 n bytes
     HIPCHK(c, c->tmp_off.ensure(std::max(n + S + 2, tree_scratch_u32(n))));
@@ -94,7 +93,7 @@ Cells cells_view(fdx_ctx *c) {
     v.level = c->c_level.p; v.begin = c->c_begin.p; v.count = c->c_count.p;
     v.first = c->c_first.p; v.nchild = c->c_nchild.p; v.parent = c->c_parent.p;
     v.prefix = c->c_prefix.p; v.node = c->c_node.p; v.link = c->c_link.p; v.mom = c->c_mom.p;
-    v.lvl = c->c_lvl.p; v.cap = c->cell_cap;
+    v.lvl = c->st->lvl; v.cap = c->cell_cap;
     return v;
 }
 
@@ -122,8 +121,6 @@ void mark(fdx_ctx *c, int k) {
 int read_status(fdx_ctx *c) {
     HIPCHK(c, hipMemcpyAsync(&c->hst->st, c->st, sizeof(DevStatus), hipMemcpyDeviceToHost,
                              c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->hst->lvl, c->c_lvl.p, sizeof(uint32_t) * (kLevels + 2),
-                             hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return FDX_OK;
 }
@@ -162,13 +159,14 @@ int enqueue_tree_groups(fdx_ctx *c) {
     const int S = c->nsys;
     hipStream_t s = c->stream;
     HIPCHK(c, tree_build(n, S, c->sys_off.p, c->skey, c->n_leaf, cells_view(c),
-                         (uint8_t *)c->tmp_n.p, c->tmp_off.p, c->partial.p, c->st, s));
+                         (uint8_t *)c->tmp_n.p, c->tmp_off.p, c->flag.p, c->leaf_lev.p, c->partial.p,
+                         c->st, s));
     mark(c, 3);
     HIPCHK(c, tree_moments(n, S, c->sys_off.p, c->tmp_off.p, cells_view(c), c->jp.p, s));
     mark(c, 4);
     HIPCHK(c, make_groups(n, S, c->sys_off.p, cells_view(c), c->skey, c->cube.p, c->seps.p,
                           c->n_group, groups_view(c), c->flag.p, c->gcell_at.p, c->gpos.p,
-                          c->leaf_lev.p, c->partial.p, c->st, s));
+                          c->leaf_lev.p, c->wide_list.p, c->partial.p, c->st, s));
     mark(c, 5);
     return FDX_OK;
 }
@@ -222,14 +220,13 @@ int enqueue_count(fdx_ctx *c, size_t gmax) {
     Groups gv = groups_view(c);
     if (c->cutoff > 0)
         HIPCHK(c, walk_short(false, 4, gmax, gv, cells_view(c), cutoff_args(c), c->theta * c->theta,
-                             nullptr, nullptr, 0, nullptr, c->cnt_e.p, c->cnt_s.p, c->ovf_list.p,
+                             nullptr, c->lcap.p, 0, nullptr, c->cnt_e.p, c->cnt_s.p, c->ovf_list.p,
                              c->st, s));
     else
         HIPCHK(c, walk_runs(false, gmax, gv, cells_view(c), c->theta * c->theta, nullptr,
-                            nullptr, 0, nullptr, c->cnt_e.p, c->cnt_s.p, c->ovf_list.p, nullptr,
+                            c->lcap.p, 0, nullptr, c->cnt_e.p, c->cnt_s.p, c->ovf_list.p, nullptr,
                             nullptr, c->st, s));
-    HIPCHK(c, list_caps(gmax, c->cnt_e.p, c->cnt_s.p, c->lcap.p, c->st, s));
-    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, 0, nullptr, &c->st->n_groups_c, c->partial.p,
+    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, gmax, nullptr, &c->st->n_groups_c, c->partial.p,
                               &c->st->list_total, s));
     return FDX_OK;
 }
@@ -237,7 +234,7 @@ int enqueue_count(fdx_ctx *c, size_t gmax) {
 int enqueue_sys_caps(fdx_ctx *c, size_t gmax, const uint32_t *sys_cap) {
     hipStream_t s = c->stream;
     HIPCHK(c, sys_caps(gmax, c->g_sys.p, sys_cap, c->lcap.p, c->st, s));
-    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, 0, nullptr, &c->st->n_groups_c, c->partial.p,
+    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, gmax, nullptr, &c->st->n_groups_c, c->partial.p,
                               &c->st->list_total, s));
     return FDX_OK;
 }
@@ -291,7 +288,6 @@ int enqueue_force(fdx_ctx *c, size_t gmax) {
         // groups too wide for group-relative FP32: evaluated again by the FP64 kernel, which
         // overwrites their rows (one persistent pass over the device-side list; empty when no
         // group is wide)
-        HIPCHK(c, wide_group_list(gmax, gv, c->wide_list.p, c->st, s));
         ForceArgs fw = fa;
         fw.fp32 = false;
         fw.near = nullptr;
@@ -338,7 +334,6 @@ int enqueue_fused(fdx_ctx *c, size_t gmax, bool capture) {
     if (fp32) {
         // groups too wide for group-relative FP32: a second pass of the FP64 kernel over the
         // device-side list of them (empty when no group is wide)
-        HIPCHK(c, wide_group_list(gmax, gv, c->wide_list.p, c->st, s));
         FusedArgs fw = fa;
         fw.order = c->wide_list.p;
         fw.count = &c->st->wide_groups;
@@ -453,11 +448,11 @@ void finish_stats(fdx_ctx *c) {
     fdx_stats &o = c->stats;
     const DevStatus &h = c->hst->st;
     o.n = c->n; o.n_sys = c->nsys;
-    o.n_cells = c->hst->lvl[kLevels + 1];
+    o.n_cells = c->hst->st.lvl[kLevels + 1];
     o.n_groups = h.n_groups;
     int depth = 0;
     for (int l = 0; l <= kLevels; l++)
-        if (c->hst->lvl[l + 1] > c->hst->lvl[l]) depth = l;
+        if (c->hst->st.lvl[l + 1] > c->hst->st.lvl[l]) depth = l;
     o.depth = depth;
     o.n_leaf = c->n_leaf; o.n_group = c->n_group; o.flags = c->flags; o.theta = c->theta;
     o.shape = ext_force_variant(c);

@@ -41,7 +41,6 @@ struct DBuf {
 
 struct HostStatus {
     DevStatus st;
-    uint32_t lvl[kLevels + 2];
 };
 
 }  // namespace fdx
@@ -80,7 +79,7 @@ struct fdx_ctx {
     fdx::DBuf<double> seps;
 
     // tree
-    fdx::DBuf<uint32_t> c_level, c_begin, c_count, c_first, c_nchild, c_parent, c_lvl;
+    fdx::DBuf<uint32_t> c_level, c_begin, c_count, c_first, c_nchild, c_parent;
     fdx::DBuf<uint64_t> c_prefix;
     fdx::DBuf<uint4> c_node;
     fdx::DBuf<uint2> c_link;
@@ -144,7 +143,7 @@ struct fdx_ctx {
         f(bbox_u); f(key); f(key_alt); f(cube);
         f(perm); f(perm_alt); f(inv); f(rs_scratch); f(sys_carry); f(partial);
         f(jp); f(packed); f(seps);
-        f(c_level); f(c_begin); f(c_count); f(c_first); f(c_nchild); f(c_parent); f(c_lvl);
+        f(c_level); f(c_begin); f(c_count); f(c_first); f(c_nchild); f(c_parent);
         f(c_prefix); f(c_node); f(c_link); f(c_mom); f(tmp_n); f(tmp_off);
         f(g_cell); f(g_begin); f(g_count); f(g_sys); f(g_box); f(flag); f(gcell_at); f(gpos);
         f(g_wide); f(wide_list); f(leaf_lev); f(g_centre); f(g_far); f(g_near);

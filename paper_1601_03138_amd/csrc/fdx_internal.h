@@ -35,7 +35,7 @@ struct DevStatus {
     uint32_t xcd_head[8];     // persistent force kernel: next slot of each XCD's queue
     uint64_t spill_used;      // fill walk: entries taken after list_total by relocated lists
     uint32_t spilled;         // fill walk: groups whose list was relocated there
-    uint32_t pad2_;
+    uint32_t lvl[kLevels + 2];         // first cell of each level (Cells::lvl)
 };
 
 // any device-reported condition that makes this evaluation's forces incomplete
@@ -86,7 +86,7 @@ hipError_t unsort_forces(size_t n, const double4 *fs, const uint32_t *inv, doubl
                          double *ay, double *az, double *pot, hipStream_t s);
 
 // scan: exclusive prefix sums of u32 counts.  The element count is n_host, or, if lo/hi are
-// given, (*hi - *lo) read on the device.  partial must hold kScanBlocks + 1 entries.
+// given, (*hi - *lo) read on the device; n_host is then an upper bound of it, or 0 (unknown).  partial must hold kScanBlocks + 1 entries.
 constexpr int kScanBlocks = 512;
 hipError_t scan_u32_to_u32(const uint32_t *in, uint32_t *out, size_t n_host,
                            const uint32_t *lo, const uint32_t *hi, uint64_t *partial,
@@ -130,11 +130,12 @@ hipError_t gather_sorted(size_t n, const uint32_t *perm, const double4 *packed,
 // at 2^20, 90 and 119 us at 2^24 (16: 95 and 148; 2: 96 and 138).
 constexpr int kTileRounds = 4;
 constexpr int kTileW = kTileRounds * 64;
-// scratch words tree_build needs besides 3 n bytes
+// scratch words tree_build needs besides 3 n bytes.  It also prepares make_groups: flag (n words) is
+// cleared, plev (n bytes) receives the level of every particle's leaf.
 size_t tree_scratch_u32(size_t n);
 hipError_t tree_build(size_t n, int nsys, const int64_t *sys_off, const uint64_t *skey,
-                      int n_leaf, Cells c, uint8_t *bytes, uint32_t *scratch,
-                      uint64_t *partial, DevStatus *st, hipStream_t s);
+                      int n_leaf, Cells c, uint8_t *bytes, uint32_t *scratch, uint32_t *flag,
+                      uint8_t *plev, uint64_t *partial, DevStatus *st, hipStream_t s);
 // moments of all cells; scratch as tree_build left it
 hipError_t tree_moments(size_t n, int nsys, const int64_t *sys_off, const uint32_t *scratch, Cells c,
                         const double4 *jp, hipStream_t s);
@@ -142,19 +143,18 @@ hipError_t tree_moments(size_t n, int nsys, const int64_t *sys_off, const uint32
 // leaf below its cell, S the cell side and eps_min the smallest softening among its members,
 // a group is wide iff 9 u min(S / eps_min, 2^d) > 1e-4 (u = 2^-24), i.e. FP32 rounding of
 // coordinates taken relative to the group's centre could move a close pair's force by more
-// than 1e-4 of itself.  plev (n bytes) receives the level of every particle's leaf.
+// than 1e-4 of itself.  flag and plev as tree_build left them.  The wide groups are listed in
+// wide_list (any order; count in st->wide_groups).
 hipError_t make_groups(size_t n, int nsys, const int64_t *sys_off, Cells c,
                        const uint64_t *skey, const double *cube, const double *seps,
                        int n_group, Groups g, uint32_t *flag, uint32_t *gcell_at, uint32_t *gpos,
-                       uint8_t *plev, uint64_t *partial, DevStatus *st, hipStream_t s);
-// list of the wide groups (any order; count in st->wide_groups) and a reset of the persistent
-// queue head for the pass that evaluates them
-hipError_t wide_group_list(size_t gmax, const Groups g, uint32_t *list, DevStatus *st,
-                           hipStream_t s);
+                       const uint8_t *plev, uint32_t *wide_list, uint64_t *partial, DevStatus *st,
+                       hipStream_t s);
 
 // walk: count (fill = false) or fill (fill = true) the interaction lists.
 // seg[g]/cap[g] = start and capacity of group g's segment in `list`; EPJ entries grow from
-// the front, SPJ entries from the back.  cnt_e/cnt_s receive the exact counts.
+// the front, SPJ entries from the back.  cnt_e/cnt_s receive the exact counts, and a count
+// walk's cap (unless null) their sum.
 // A group whose entries do not fit its segment (or whose segment passes list_cap) writes
 // nothing, gets zero counts and is appended to ovf_list (st->list_overflow counts them).
 // sel (optional, with nsel): walk only the listed groups (predictor re-walk).
@@ -205,7 +205,7 @@ hipError_t walk_runs(bool fill, size_t gmax, const Groups g, const Cells c, doub
 // or the TreePM cutoff walk (kind 4: cells beyond sa.r_fixed dropped, opening angle theta
 // for the rest)
 hipError_t walk_short(bool fill, int kind, size_t gmax, const Groups g, const Cells c,
-                      const ShortArgs sa, double theta2, const uint64_t *seg, const uint32_t *cap,
+                      const ShortArgs sa, double theta2, const uint64_t *seg, uint32_t *cap,
                       uint64_t list_cap, uint32_t *list, uint32_t *cnt_e, uint32_t *cnt_s,
                       uint32_t *ovf_list, DevStatus *st, hipStream_t s);
 // SPH density on short-range lists (k_sph.hip): support radii in sorted order (h given, else
@@ -295,8 +295,6 @@ hipError_t queue_bounds(size_t gmax, const uint32_t *gcount, const float *y,
 hipError_t fused(size_t gmax, const FusedArgs &a, bool fp32, bool quad, int n_group,
                  hipStream_t s);
 
-hipError_t list_caps(size_t gmax, const uint32_t *cnt_e, const uint32_t *cnt_s, uint32_t *cap,
-                     DevStatus *st, hipStream_t s);
 // lists out of their segments: epj[oe[g] ...] and spj[os[g] ...] (offsets exclusive sums)
 hipError_t compact_lists(size_t G, const uint64_t *seg, const uint32_t *cap,
                          const uint32_t *cnt_e, const uint32_t *cnt_s, const uint64_t *oe,

@@ -124,7 +124,7 @@ constexpr uint64_t kSizedBudget = 1ull << 32;
 // grown: growing reallocates the group arrays and drops their contents.
 static int graph_headroom(fdx_ctx *c, GraphState *g) {
     const DevStatus h = c->hst->st;         // the last evaluation's tree and lists
-    const uint32_t ncell = c->hst->lvl[kLevels + 1];
+    const uint32_t ncell = c->hst->st.lvl[kLevels + 1];
     const int S = c->nsys;
     const uint64_t pct = c->ext.graph_margin_pct;
     const bool try_sized = S > 1 && c->have_lists && pct > 0 && !(c->flags & FDX_FUSED);

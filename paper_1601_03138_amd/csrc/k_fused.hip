@@ -420,8 +420,9 @@ k_fused(FusedArgs a) {
 // counts, or members x predicted list length (y = predicted ln length), or members
 __global__ void k_queue_cost(const uint32_t *ngroups_c, const uint32_t *gcount, const float *y,
                              const uint32_t *cnt_e, const uint32_t *cnt_s, float ws,
-                             uint32_t *cost) {
+                             uint32_t *cost, DevStatus *st) {
     const uint32_t G = *ngroups_c;
+    if (gtid() == 0) st->queue_head = 0;         // for the pass over the wide groups
     for (size_t gi = gtid(); gi < G; gi += gstride()) {
         float c = (float)gcount[gi];
         if (cnt_e) c *= (float)cnt_e[gi] + ws * (float)cnt_s[gi];
@@ -473,8 +474,8 @@ hipError_t queue_bounds(size_t gmax, const uint32_t *gcount, const float *y,
     size_t b = (gmax + 255) / 256;
     b = b < 1 ? 1 : (b > 4096 ? 4096 : b);
     hipLaunchKernelGGL(k_queue_cost, dim3((unsigned)b), dim3(256), 0, s, &st->n_groups_c, gcount,
-                       y, cnt_e, cnt_s, ws, cost);
-    hipError_t e = scan_u32_to_u64(cost, pre, 0, nullptr, &st->n_groups_c, partial, pre + gmax, s);
+                       y, cnt_e, cnt_s, ws, cost, st);
+    hipError_t e = scan_u32_to_u64(cost, pre, gmax, nullptr, &st->n_groups_c, partial, pre + gmax, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fused_bounds, dim3(1), dim3(64), 0, s, &st->n_groups_c, pre, pre + gmax,
                        bounds);

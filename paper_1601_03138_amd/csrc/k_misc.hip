@@ -205,9 +205,45 @@ k_scan_down32(const uint32_t *in, uint32_t *out, size_t n_host, const uint32_t *
     }
 }
 
+// A few thousand elements in one launch of one workgroup (any count is right): three launches that
+// wait for each other are bound by their start, 4.6 us each.  336 elements 2.8 us, 4096 4.1 us, 16384
+// 13.1 us, against 14.
+constexpr size_t kScanOne = 16384;
+constexpr int kOneThreads = 1024, kOneItems = 4;
+template <class T>
+__global__ void __launch_bounds__(kOneThreads)
+k_scan_one(const uint32_t *in, T *out, size_t n_host, const uint32_t *lo, const uint32_t *hi,
+           T *total) {
+    __shared__ uint64_t lds[kOneThreads / kWave];
+    const size_t n = scan_count(n_host, lo, hi);
+    uint64_t base = 0;
+    for (size_t t0 = 0; t0 < n; t0 += kOneThreads * kOneItems) {
+        const size_t i0 = t0 + (size_t)threadIdx.x * kOneItems;
+        uint32_t v[kOneItems];
+        uint64_t s = 0, tot;
+#pragma unroll
+        for (int k = 0; k < kOneItems; k++) v[k] = i0 + k < n ? in[i0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < kOneItems; k++) s += v[k];
+        uint64_t e = base + block_excl_scan<kOneThreads>(s, lds, &tot);
+#pragma unroll
+        for (int k = 0; k < kOneItems; k++) {
+            if (i0 + k < n) out[i0 + k] = (T)e;
+            e += v[k];
+        }
+        base += tot;
+    }
+    if (threadIdx.x == 0 && total) *total = (T)base;
+}
+
 template <class T>
 hipError_t scan_impl(const uint32_t *in, T *out, size_t n_host, const uint32_t *lo,
                      const uint32_t *hi, uint64_t *partial, T *total, hipStream_t s) {
+    if (n_host <= kScanOne && (n_host || !hi)) {
+        hipLaunchKernelGGL(k_scan_one<T>, dim3(1), dim3(kOneThreads), 0, s, in, out, n_host, lo, hi,
+                           total);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_scan_reduce, dim3(kScanBlocks), dim3(kThreads), 0, s, in, n_host, lo,
                        hi, partial);
     hipLaunchKernelGGL(k_scan_top<T>, dim3(1), dim3(kScanBlocks), 0, s, partial, total);

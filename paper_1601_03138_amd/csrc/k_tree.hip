@@ -100,13 +100,14 @@ __device__ __forceinline__ int shared_levels(uint64_t a, uint64_t b) {
     return x ? (__clzll((long long)x) - 1) / 3 : kLevels;
 }
 
-// per position: lo(r) and c(r)
+// per position: lo(r) and c(r); the group flags start from zero
 __global__ void k_cells_prefix(size_t n, int nsys, const int64_t *off, const uint64_t *skey,
-                               int n_leaf, uint8_t *lo8, int8_t *c8) {
+                               int n_leaf, uint8_t *lo8, int8_t *c8, uint32_t *flag) {
     for (size_t r = gtid(); r < n; r += gstride()) {
         const int sys = system_of(off, nsys, r);
         const size_t s0 = (size_t)off[sys], s1 = (size_t)off[sys + 1];
         const uint64_t k = skey[r];
+        flag[r] = 0;
         lo8[r] = (uint8_t)(r == s0 ? 1 : shared_levels(skey[r - 1], k) + 1);
         c8[r] = (int8_t)(r + (size_t)n_leaf < s1 ? shared_levels(k, skey[r + n_leaf]) : -1);
     }
@@ -145,37 +146,34 @@ k_cells_count(size_t n, int nsys, const int64_t *off, int n_leaf, const uint8_t 
     if (lane < kLevels) wcount[(size_t)lane * ntiles + tile] = cnt;
 }
 
-// level starts from the scanned counts; if the cells of every level do not fit the capacity,
-// keep the levels that do (the deepest kept level's cells become leaves) and flag it
-__global__ void k_cells_levels(int nsys, uint32_t ntiles, const uint32_t *woff,
-                               const uint32_t *total, Cells c, DevStatus *st) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    uint32_t lv[kLevels + 2];
-    lv[0] = 0;
-    lv[1] = (uint32_t)nsys;
-    for (int L = 1; L <= kLevels; L++) {
-        const uint32_t nxt = L < kLevels ? woff[(size_t)L * ntiles] : *total;
-        lv[L + 1] = (uint32_t)nsys + nxt;
-    }
-    int top = kLevels;
-    while (top > 0 && lv[top + 1] > c.cap) top--;
-    const bool ovf = top < kLevels && lv[kLevels + 1] > c.cap;
-    for (int L = 0; L <= kLevels + 1; L++) c.lvl[L] = L <= top + 1 ? lv[L] : lv[top + 1];
-    st->cell_overflow = ovf ? 1u : 0u;
-    st->top_level = (uint32_t)top;
-}
-
 // write the cells of levels 1..top starting in each wave tile: level, prefix, begin, and
-// first-child links (a split cell's first child starts at the same position one level down)
+// first-child links (a split cell's first child starts at the same position one level down).
+// Level starts from the scanned counts, in every wave (lane L: level L) and stored by the first; if
+// the cells of every level do not fit the capacity, the levels that do are kept (the deepest kept
+// level's cells become leaves) and it is flagged.
 __global__ void __launch_bounds__(kThreads)
 k_cells_emit(size_t n, int nsys, const int64_t *off, const uint64_t *skey, const uint8_t *lo8,
-             const uint8_t *hi8, uint32_t ntiles, const uint32_t *woff, Cells c,
-             const DevStatus *st) {
+             const uint8_t *hi8, uint32_t ntiles, const uint32_t *woff, const uint32_t *total,
+             Cells c, DevStatus *st) {
     const size_t tile = gtid() / kWave;
     if (tile >= ntiles) return;
     const int lane = lane_id();
     const uint64_t lt = lanemask_lt();
-    const int top = (int)st->top_level;
+    uint32_t lv = 0;
+    if (lane >= 1 && lane <= kLevels + 1)
+        lv = (uint32_t)nsys + (lane <= kLevels ? woff[(size_t)(lane - 1) * ntiles] : *total);
+    // levels 1.. end at lane level + 1; the first that ends past the capacity is dropped with all
+    // below it
+    const uint64_t past = __ballot(lane >= 2 && lane <= kLevels + 1 && lv > c.cap);
+    const int top = past ? __builtin_ctzll(past) - 2 : kLevels;
+    if (tile == 0) {
+        const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)lv, top + 1);
+        if (lane <= kLevels + 1) c.lvl[lane] = lane <= top + 1 ? lv : end;
+        if (lane == 0) {
+            st->cell_overflow = top < kLevels ? 1u : 0u;
+            st->top_level = (uint32_t)top;
+        }
+    }
     uint8_t lo[kTileRounds], hi[kTileRounds];
     uint32_t prev[kTileRounds];
     int lmin = kLevels + 1, lmax = 0;
@@ -220,8 +218,10 @@ k_cells_emit(size_t n, int nsys, const int64_t *off, const uint64_t *skey, const
 // per cell: particle count (end of the run of keys sharing the cell's L digits, found by a
 // galloping search bounded by the system's end), children (the at most 8 cells of level
 // L + 1 from the first child on that start before the end) and their parent link, and the
-// walk views (half-grid centre + level/nchild, leaf or internal link)
-__global__ void k_cells_finish(int nsys, const int64_t *off, const uint64_t *skey, Cells c) {
+// walk views (half-grid centre + level/nchild, leaf or internal link); leaves also write their level
+// for each of their particles
+__global__ void k_cells_finish(int nsys, const int64_t *off, const uint64_t *skey, Cells c,
+                               uint8_t *plev) {
     const uint32_t nc = c.lvl[kLevels + 1];
     for (size_t k = gtid(); k < nc; k += gstride()) {
         const uint32_t cid = (uint32_t)k;
@@ -267,6 +267,8 @@ __global__ void k_cells_finish(int nsys, const int64_t *off, const uint64_t *ske
         nd.w = L | (nch << 8);
         c.node[cid] = nd;
         c.link[cid] = nch ? make_uint2(first, cnt) : make_uint2(b, cnt);
+        if (!nch)
+            for (uint32_t r = b; r < b + cnt; r++) plev[r] = (uint8_t)L;
     }
 }
 
@@ -406,25 +408,6 @@ __global__ void k_group_emit(size_t n, int n_group, Cells c, const uint32_t *fla
     }
 }
 
-// level of every particle's leaf (leaves partition the particles)
-__global__ void k_leaf_level(Cells c, uint8_t *plev) {
-    const uint32_t nc = min(c.lvl[kLevels + 1], c.cap);
-    for (size_t k = gtid(); k < nc; k += gstride()) {
-        if (c.nchild[k] != 0) continue;
-        const uint32_t b = c.begin[k], e = b + c.count[k];
-        const uint8_t l = (uint8_t)c.level[k];
-        for (uint32_t r = b; r < e; r++) plev[r] = l;
-    }
-}
-
-// groups flagged wide, appended in any order (each is evaluated on its own); the counter
-// starts from zero
-__global__ void k_wide_list(const uint32_t *ngroups_c, Groups g, uint32_t *list, DevStatus *st) {
-    const uint32_t G = *ngroups_c;
-    for (size_t gi = gtid(); gi < G; gi += gstride())
-        if (g.wide[gi]) list[atomicAdd(&st->wide_groups, 1u)] = (uint32_t)gi;
-}
-
 // Per group: the integer box of its members' keys, its deepest member leaf level, its smallest
 // softening, its system, the centre of its cell and the wide flag.  Four groups per wave, one
 // per 16-lane row: the members are read 16 at a time, the reductions are four DPP lane moves
@@ -434,7 +417,7 @@ __global__ void k_wide_list(const uint32_t *ngroups_c, Groups g, uint32_t *list,
 __global__ void __launch_bounds__(kThreads)
 k_group_geom(const uint32_t *ngroups, int nsys, const int64_t *off, Cells c,
              const uint64_t *skey, const double *cube, const double *seps, const uint8_t *plev,
-             Groups g, DevStatus *st) {
+             Groups g, uint32_t *wide_list, DevStatus *st) {
     const uint32_t G = min(*ngroups, g.cap);
     if (gtid() == 0) {
         st->n_groups_c = G;
@@ -489,6 +472,8 @@ k_group_geom(const uint32_t *ngroups, int nsys, const int64_t *off, Cells c,
             const double m = fmin(side / emin, span);
             const bool wide = (9.0 * 5.9604644775390625e-8) * m > 1e-4;
             g.wide[gi] = wide ? 1u : 0u;
+            // listed in any order (each is evaluated on its own)
+            if (wide) wide_list[atomicAdd(&st->wide_groups, 1u)] = (uint32_t)gi;
             if (g.far) {
                 FarGeom f;
                 double d2 = 0.0, ec[3];
@@ -533,8 +518,8 @@ size_t tree_scratch_u32(size_t n) {
 }
 
 hipError_t tree_build(size_t n, int nsys, const int64_t *sys_off, const uint64_t *skey,
-                      int n_leaf, Cells c, uint8_t *bytes, uint32_t *scratch,
-                      uint64_t *partial, DevStatus *st, hipStream_t s) {
+                      int n_leaf, Cells c, uint8_t *bytes, uint32_t *scratch, uint32_t *flag,
+                      uint8_t *plev, uint64_t *partial, DevStatus *st, hipStream_t s) {
     hipLaunchKernelGGL(k_tree_init, dim3((nsys + 255) / 256), dim3(256), 0, s, nsys, sys_off, c, st);
     const size_t ntiles = (n + kTileW - 1) / kTileW;
     uint8_t *lo8 = bytes, *hi8 = bytes + n;
@@ -543,20 +528,18 @@ hipError_t tree_build(size_t n, int nsys, const int64_t *sys_off, const uint64_t
     uint32_t *total = woff + (size_t)kLevels * ntiles;
     if (n) {
         hipLaunchKernelGGL(k_cells_prefix, dim3(grid_for(n)), dim3(kThreads), 0, s, n, nsys,
-                           sys_off, skey, n_leaf, lo8, c8);
+                           sys_off, skey, n_leaf, lo8, c8, flag);
         const unsigned tb = (unsigned)((ntiles * kWave + kThreads - 1) / kThreads);
         hipLaunchKernelGGL(k_cells_count, dim3(tb), dim3(kThreads), 0, s, n, nsys, sys_off,
                            n_leaf, lo8, c8, hi8, (uint32_t)ntiles, wcount);
         hipError_t e = scan_u32_to_u32(wcount, woff, (size_t)kLevels * ntiles, nullptr, nullptr,
                                        partial, total, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_cells_levels, dim3(1), dim3(64), 0, s, nsys, (uint32_t)ntiles, woff,
-                           total, c, st);
         hipLaunchKernelGGL(k_cells_emit, dim3(tb), dim3(kThreads), 0, s, n, nsys, sys_off, skey,
-                           lo8, hi8, (uint32_t)ntiles, woff, c, st);
+                           lo8, hi8, (uint32_t)ntiles, woff, total, c, st);
     }
     hipLaunchKernelGGL(k_cells_finish, dim3(grid_for(c.cap, 8192)), dim3(kThreads), 0, s, nsys,
-                       sys_off, skey, c);
+                       sys_off, skey, c, plev);
     return hipGetLastError();
 }
 
@@ -576,28 +559,17 @@ hipError_t tree_moments(size_t n, int nsys, const int64_t *sys_off, const uint32
 hipError_t make_groups(size_t n, int nsys, const int64_t *sys_off, Cells c,
                        const uint64_t *skey, const double *cube, const double *seps,
                        int n_group, Groups g, uint32_t *flag, uint32_t *gcell_at, uint32_t *gpos,
-                       uint8_t *plev, uint64_t *partial, DevStatus *st, hipStream_t s) {
-    hipError_t e = fill_u32(flag, 0u, n, s);
-    if (e != hipSuccess) return e;
+                       const uint8_t *plev, uint32_t *wide_list, uint64_t *partial, DevStatus *st,
+                       hipStream_t s) {
     hipLaunchKernelGGL(k_group_flags, dim3(grid_for(c.cap, 8192)), dim3(kThreads), 0, s, c,
                        n_group, flag, gcell_at);
-    e = scan_u32_to_u32(flag, gpos, n, nullptr, nullptr, partial, &st->n_groups, s);
+    hipError_t e = scan_u32_to_u32(flag, gpos, n, nullptr, nullptr, partial, &st->n_groups, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_group_emit, dim3(grid_for(n)), dim3(kThreads), 0, s, n, n_group, c, flag,
                        gcell_at, gpos, g);
-    hipLaunchKernelGGL(k_leaf_level, dim3(grid_for(c.cap, 8192)), dim3(kThreads), 0, s, c, plev);
     hipLaunchKernelGGL(k_group_geom, dim3(grid_for(16 * (size_t)g.cap, 4096)), dim3(kThreads), 0, s,
-                       &st->n_groups, nsys, sys_off, c, skey, cube, seps, plev, g, st);
-    return hipGetLastError();
-}
-
-hipError_t wide_group_list(size_t gmax, const Groups g, uint32_t *list, DevStatus *st,
-                           hipStream_t s) {
-    hipError_t e = fill_u32(&st->wide_groups, 0u, 1, s);
-    if (e == hipSuccess) e = fill_u32(&st->queue_head, 0u, 1, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wide_list, dim3(grid_for(gmax + 1, 4096)), dim3(kThreads), 0, s,
-                       &st->n_groups_c, g, list, st);
+                       &st->n_groups, nsys, sys_off, c, skey, cube, seps, plev, g,
+                       wide_list, st);
     return hipGetLastError();
 }
 

@@ -228,6 +228,7 @@ k_walk(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *link, 
             } else {
                 cnt_e[gi] = ne;
                 cnt_s[gi] = ns;
+                if (!FILL && cap) cap[gi] = ne + ns;
             }
         }
     }
@@ -528,17 +529,11 @@ k_walk_runs(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *l
                 } else {
                     cnt_e[gi] = ne;
                     cnt_s[gi] = ns;
+                    if (!FILL && cap) cap[gi] = ne + ns;
                 }
             }
         }
     }
-}
-
-// cap[g] = |EPJ| + |SPJ| (exact segment sizes)
-__global__ void k_list_caps(const uint32_t *ngroups, uint32_t gmax, const uint32_t *cnt_e,
-                            const uint32_t *cnt_s, uint32_t *cap) {
-    const uint32_t G = min(*ngroups, gmax);
-    for (size_t gi = gtid(); gi < G; gi += gstride()) cap[gi] = cnt_e[gi] + cnt_s[gi];
 }
 
 // cap[g] = sys_cap[system of g]: per-system segment sizes (a system's particle count bounds
@@ -581,6 +576,7 @@ __global__ void __launch_bounds__(kThreads)
 k_list_stats(const uint32_t *ngroups, uint32_t gmax, const uint32_t *gcount,
              const uint32_t *cnt_e, const uint32_t *cnt_s, DevStatus *st) {
     const uint32_t G = min(*ngroups, gmax);
+    if (gtid() == 0) st->queue_head = 0;         // for the pass over the wide groups
     uint64_t e = 0, s = 0, pp = 0, pc = 0;
     for (size_t gi = gtid(); gi < G; gi += gstride()) {
         const uint64_t ni = gcount[gi];
@@ -845,11 +841,10 @@ hipError_t walk_runs(bool fill, size_t gmax, const Groups g, const Cells c, doub
 
 hipError_t walk_short(bool fill, int kind, size_t gmax, const Groups g, const Cells c,
                       const ShortArgs sa, double theta2, const uint64_t *seg_c,
-                      const uint32_t *cap_c, uint64_t list_cap, uint32_t *list, uint32_t *cnt_e,
+                      uint32_t *cap, uint64_t list_cap, uint32_t *list, uint32_t *cnt_e,
                       uint32_t *cnt_s, uint32_t *ovf_list, DevStatus *st, hipStream_t s) {
-    // short walks never relocate a list, so the segment arrays are only read
+    // short walks never relocate a list, so the segment starts are only read
     uint64_t *seg = const_cast<uint64_t *>(seg_c);
-    uint32_t *cap = const_cast<uint32_t *>(cap_c);
     switch (kind) {
         case 1: launch_walk<1>(fill, gmax, g, c, 0.0, seg, cap, list_cap, list, cnt_e, cnt_s,
                                ovf_list, nullptr, nullptr, st, sa, s); break;
@@ -860,15 +855,6 @@ hipError_t walk_short(bool fill, int kind, size_t gmax, const Groups g, const Ce
         default: launch_walk<4>(fill, gmax, g, c, theta2, seg, cap, list_cap, list, cnt_e, cnt_s,
                                 ovf_list, nullptr, nullptr, st, sa, s); break;
     }
-    return hipGetLastError();
-}
-
-hipError_t list_caps(size_t gmax, const uint32_t *cnt_e, const uint32_t *cnt_s, uint32_t *cap,
-                     DevStatus *st, hipStream_t s) {
-    size_t b = (gmax + kThreads - 1) / kThreads;
-    b = b < 1 ? 1 : (b > 8192 ? 8192 : b);
-    hipLaunchKernelGGL(k_list_caps, dim3((unsigned)b), dim3(kThreads), 0, s, &st->n_groups_c,
-                       (uint32_t)gmax, cnt_e, cnt_s, cap);
     return hipGetLastError();
 }
 

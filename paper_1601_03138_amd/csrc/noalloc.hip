@@ -175,7 +175,6 @@ int fdx_calc_force_noalloc(int device, void *hip_stream, int64_t n, const double
     cv.take(c.c_first, ccap); cv.take(c.c_nchild, ccap); cv.take(c.c_parent, ccap);
     cv.take(c.c_prefix, ccap); cv.take(c.c_node, ccap); cv.take(c.c_link, ccap);
     cv.take(c.c_mom, 10 * (size_t)ccap);
-    cv.take(c.c_lvl, kLevels + 2);
     cv.take(c.tmp_n, N + S + 1);
     cv.take(c.tmp_off, std::max(N + S + 2, tree_scratch_u32(N)));
     c.cell_cap = ccap;

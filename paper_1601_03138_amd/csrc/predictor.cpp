@@ -83,7 +83,7 @@ int ext_predicted_walk(fdx_ctx *c, uint32_t G) {
     HIPCHK(c, pred_caps(G, p->y.p, p->margin, std::max<uint32_t>(cap_max, 1), c->lcap.p, c->st, s));
     mark(c, 9);
     c->predict_marked = (c->flags & FDX_TIMING) != 0;
-    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, 0, nullptr, &c->st->n_groups_c, c->partial.p,
+    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, G, nullptr, &c->st->n_groups_c, c->partial.p,
                               &c->st->list_total, s));
     int r = read_status(c);
     if (r) return r;

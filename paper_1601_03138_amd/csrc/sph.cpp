@@ -99,10 +99,9 @@ int fdx_calc_density(fdx_ctx *c, int32_t mode, double r_cut, const double *h, in
     }
     const int kind = mode == FDX_CUT_SCATTER ? 2 : (mode == FDX_CUT_SYMMETRIC ? 3 : 1);
     // count pass, segment sizes and offsets (total in st->list_total), one read, fill pass
-    HIPCHK(c, walk_short(false, kind, G, gv, cv, sa, 0.0, nullptr, nullptr, 0, nullptr, c->cnt_e.p,
+    HIPCHK(c, walk_short(false, kind, G, gv, cv, sa, 0.0, nullptr, c->lcap.p, 0, nullptr, c->cnt_e.p,
                          c->cnt_s.p, nullptr, c->st, s));
-    HIPCHK(c, list_caps(G, c->cnt_e.p, c->cnt_s.p, c->lcap.p, c->st, s));
-    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, 0, nullptr, &c->st->n_groups_c, c->partial.p,
+    HIPCHK(c, scan_u32_to_u64(c->lcap.p, c->seg.p, G, nullptr, &c->st->n_groups_c, c->partial.p,
                               &c->st->list_total, s));
     r = read_status(c);
     if (r) return r;
