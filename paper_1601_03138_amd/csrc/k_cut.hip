@@ -37,7 +37,7 @@ struct CutArgs {
     const uint32_t *cap, *cnt_e, *cnt_s, *list, *order, *bounds, *ngroups;
     double4 *fs;
     DevStatus *st;
-    uint32_t G;
+    uint32_t G, run;
     double r_cut;
 };
 
@@ -180,8 +180,7 @@ template <class T>
 __global__ void __launch_bounds__(kSiftThreads) k_cut_direct(CutArgs a) {
     __shared__ CutSmem<T> sm;
     // XCD-aware order, as the Newtonian kernels'
-    const uint32_t chunk = (a.G + 7) / 8;
-    const uint32_t q = (blockIdx.x % 8) * chunk + blockIdx.x / 8;
+    const uint32_t q = xcd_run_block(blockIdx.x, a.run);
     if (q >= a.G) return;
     cut_group<T>(a, a.order ? a.order[q] : q, sm);
 }
@@ -207,7 +206,8 @@ template <class T>
 hipError_t launch(const CutArgs &a, bool persistent, hipStream_t s) {
     if (!persistent) {
         if (!a.G) return hipSuccess;
-        hipLaunchKernelGGL(k_cut_direct<T>, dim3(8 * ((a.G + 7) / 8)), dim3(kSiftThreads), 0, s, a);
+        hipLaunchKernelGGL(k_cut_direct<T>, dim3(xcd_run_blocks(a.G, a.run)),
+                           dim3(kSiftThreads), 0, s, a);
         return hipGetLastError();
     }
     int dev = 0, ncu = 256, per_cu = 0;
@@ -231,6 +231,7 @@ hipError_t cut_force(size_t G, const ForceArgs &fa, hipStream_t s) {
     a.order = fa.order; a.bounds = fa.bounds;
     a.ngroups = fa.count ? fa.count : &fa.st->n_groups_c;
     a.fs = fa.fs; a.st = fa.st; a.G = (uint32_t)G; a.r_cut = fa.r_cut;
+    a.run = xcd_direct_run(G, 64);        // 2^23 uniform: 64 3.30 ms, 16 3.41
     return fa.fp32 ? launch<float>(a, fa.persistent, s) : launch<double>(a, fa.persistent, s);
 }
 
