@@ -5,9 +5,12 @@
 // it, so a workgroup finishes its block level by level with a barrier between levels.  What is left
 // crosses a block boundary: at most one cell per boundary and level.  Those are finished with a thread
 // per boundary, again level by level (a cell that crosses several boundaries belongs to the first):
-// first the cells inside each group of kUpFan blocks, a workgroup per group, then the rest.  A launch per level instead waited for 22 launches of a few microseconds, most of them of
-// levels with few cells or none.  Moments of all cells (with the leaves' launch), before / now: 4096
-// particles 70 / 27 us, 21k 81 / 46 us, 2^20 137 / 98 us, 3 10^6 244 / 198 us, 2^24 705 / 673 us.
+// first the cells inside each group of kUpFan blocks, a workgroup per group, then the rest.
+//
+// Bound by the chain of loads from level to level (1.5 to 4 us each), for large sets by the bytes.  A
+// launch per level waited for 22 launches, most of them of levels with few cells or none.  Moments
+// of all cells (with the leaves' launch), before / now: 4096 particles 70 / 27 us, 21k 81 / 46 us,
+// 2^20 137 / 98 us, 3 10^6 244 / 198 us, 2^24 705 / 673 us.
 //
 // Where a block's cells of a level start is known from the build: the scanned counts per tile of
 // kTileW positions and level (tree_build's scratch).

@@ -16,9 +16,9 @@ constexpr int kSiftWaves = kSiftThreads / kWave;
 constexpr uint32_t kSiftPass = 80;        // members per pass: 20 per wave, three entries at a time
 
 // Mapping of a workgroup of four waves (TreePM): every wave has one run, or, in small groups, a
-// run and a part of the entries.  Members [first, first + n) of a group in this pass, cut into nsub runs of bs; wave w takes run
-// sub and the part-th of `parts` shares of every tile.  Its lanes are js slots of bs members:
-// slot s meets the kept entries s, s + js, ...
+// run and a part of the entries.  Members [first, first + n) of a group in this pass, cut into
+// nsub runs of bs; wave w takes run sub and the part-th of `parts` shares of every tile.  Its lanes
+// are js slots of bs members: slot s meets the kept entries s, s + js, ...
 struct SiftMap {
     uint32_t first, n, nsub, parts, bs, js, sub, part, slot, member;
     bool active;                          // this lane holds a member

@@ -107,20 +107,21 @@ ALGO_BYTES = [
     (r"^k_bbox\b", "read x, y, z", lambda N, C, G, E: 24 * N),
     (r"^k_keys\b", "read x, y, z, m; write key, index, (x, y, z, m)",
      lambda N, C, G, E: 76 * N),
-    (r"^void k_rs_hist", "read key (one 8-bit pass)", lambda N, C, G, E: 8 * N),
-    (r"^void k_rs_scatter", "read and write key + index (one pass)", lambda N, C, G, E: 24 * N),
+    (r"^k_rs_hist\b", "read key (all digits)", lambda N, C, G, E: 8 * N),
+    (r"^void k_rs_pass", "read and write key + index (one pass)", lambda N, C, G, E: 24 * N),
     (r"^k_gather_sorted\b", "read index, record, eps; write record, eps, inverse",
      lambda N, C, G, E: 88 * N),
-    (r"^k_cells_prefix\b", "read keys; write two bytes per position", lambda N, C, G, E: 10 * N),
+    (r"^k_cells_prefix\b", "read keys; write two bytes and a flag per position",
+     lambda N, C, G, E: 14 * N),
     (r"^void k_cells_count|^k_cells_count\b", "read two bytes, write one per position",
      lambda N, C, G, E: 3 * N),
     (r"^k_cells_emit\b", "read keys + three bytes per position; write 20 B per cell",
      lambda N, C, G, E: 11 * N + 20 * C),
-    (r"^k_cells_finish\b", "read 20 B, write 36 B per cell", lambda N, C, G, E: 56 * C),
-    (r"^k_moments\b", "all levels of one evaluation (one dispatch per level): write 80 B per "
+    (r"^k_cells_finish\b", "read 20 B, write 36 B per cell; write a byte per particle",
+     lambda N, C, G, E: 56 * C + N),
+    (r"^k_moments(_leaves|_across)?\b", "all dispatches of one evaluation: write 80 B per "
      "cell, read 80 B per child and 32 B per particle", lambda N, C, G, E: 160 * C + 32 * N),
     (r"^k_group_flags\b", "read counts, write flags per cell", lambda N, C, G, E: 12 * C),
-    (r"^k_leaf_level\b", "write a byte per particle", lambda N, C, G, E: 1 * N),
     (r"^void k_group_geom|^k_group_geom\b", "read member keys; write box and centre per group",
      lambda N, C, G, E: 8 * N + 48 * G),
     (r"^void k_walk(_runs)?<true(, 0)?>", "write 4 B per list entry", lambda N, C, G, E: 4 * E),
@@ -130,7 +131,7 @@ ALGO_BYTES = [
 ]
 
 
-PER_EVALUATION = {r"^k_moments\b"}
+PER_EVALUATION = {r"^k_moments(_leaves|_across)?\b"}
 # a kernel dispatched exactly once per force evaluation: counts the evaluations in a trace
 EVALUATION_MARKER = r"^k_bbox_init\b"
 
