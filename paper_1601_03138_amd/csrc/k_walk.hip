@@ -49,6 +49,11 @@ __device__ __forceinline__ bool cell_far(const uint4 nd, int bminx, int bminy, i
     return D2 > R2;
 }
 
+// Entries that a lane stores per step of a leaf.  Leaves of n_leaf 8 hold two to three particles on
+// average, so steps of 8 mostly rewrote the last entry: density fill walk at 2^24 5.50 ms, 4.98 with 4
+// (4.84 with 2, which larger leaves pay for), TreePM 1.16 and 1.12 ms.
+constexpr uint32_t kEntryChunk = 4;
+
 // How many of lc entries from slot e0 on fit a segment of capg.  The difference is kept apart from
 // the comparison: the compiler (clang 22, ROCm 7.2) otherwise drops the comparison, takes the
 // difference as non-negative, and a list that has outgrown its segment runs on behind it.
@@ -161,7 +166,7 @@ k_walk(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *link, 
                 ctot = (uint32_t)__builtin_amdgcn_readlane((int)ci, kWave - 1);
                 lex = li - lc; cex = ci - cc;
             }
-            // the stores of a lane run in unrolled chunks of 8 with immediate offsets (the
+            // the stores of a lane run in unrolled chunks with immediate offsets (the
             // capacity bound hoisted out of the chunk), so a wave spends a few instructions
             // per slot instead of a masked loop iteration; no store is predicated (a slot past
             // the lane's count rewrites its last slot with the same value), which keeps the
@@ -171,9 +176,9 @@ k_walk(const uint32_t *ngroups, Groups g, const uint4 *node, const uint2 *link, 
                 const uint32_t nw = fitting(lc, e0, capg);
                 uint32_t *dst = list + base + e0;
                 // unconditional stores: slots past nw rewrite slot nw - 1 with its own value
-                for (uint32_t k0 = 0; k0 < nw; k0 += 8) {
+                for (uint32_t k0 = 0; k0 < nw; k0 += kEntryChunk) {
 #pragma unroll
-                    for (uint32_t k = 0; k < 8; k++) {
+                    for (uint32_t k = 0; k < kEntryChunk; k++) {
                         const uint32_t j = min(k0 + k, nw - 1);
                         dst[j] = lk.x + j;
                     }
@@ -351,9 +356,9 @@ __device__ __forceinline__ int run_stack(uint32_t *stk, uint32_t sp, uint32_t *f
                 const uint32_t nw = fitting(lc, e0, capg[k]);
                 uint32_t *dst = list + base[k] + e0;
                 // unconditional stores: slots past nw rewrite slot nw - 1 with its own value
-                for (uint32_t k0 = 0; k0 < nw; k0 += 8) {
+                for (uint32_t k0 = 0; k0 < nw; k0 += kEntryChunk) {
 #pragma unroll
-                    for (uint32_t u = 0; u < 8; u++) {
+                    for (uint32_t u = 0; u < kEntryChunk; u++) {
                         const uint32_t j = min(k0 + u, nw - 1);
                         dst[j] = lk.x + j;
                     }
