@@ -847,6 +847,7 @@ int fdx_get_groups(fdx_ctx *c, uint32_t *cell, uint32_t *begin, uint32_t *count,
 int fdx_get_lists(fdx_ctx *c, uint32_t *n_epj, uint32_t *n_spj, uint32_t *epj, uint32_t *spj) {
     FDX_ABI_TRY
     if (!c) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     if (!c->have_counts) return fail(c, FDX_ESTATE, "no walk done on the current groups");
     if ((epj || spj) && !c->have_lists)
         return fail(c, FDX_ESTATE, "the last evaluation (FDX_FUSED) stored no lists: call "

@@ -202,6 +202,7 @@ int fdx_get_exchange_counts(fdx_ctx *c, uint32_t *n_epj, uint32_t *n_spj) {
 int fdx_get_exchange_lists(fdx_ctx *c, uint32_t *epj, uint32_t *spj) {
     FDX_ABI_TRY
     if (!c) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     int r = check_built(c);
     if (r) return r;
     ExchangeState *x = static_cast<ExchangeState *>(c->ext.exch);

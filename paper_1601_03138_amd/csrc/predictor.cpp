@@ -198,6 +198,7 @@ int fdx_mlp_params(void) { return kMlpParams; }
 int fdx_predictor_features(fdx_ctx *c, float *X) {
     FDX_ABI_TRY
     if (!c || !X) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     if (!c->skey) return fail(c, FDX_ESTATE, "no tree built");
     Pred *p = pred_of(c);
     const size_t G = (size_t)c->stats.n_groups;
@@ -220,6 +221,7 @@ int fdx_predictor_features(fdx_ctx *c, float *X) {
 int fdx_mlp_forward(fdx_ctx *c, const float *P, const float *X, int64_t n, float *y) {
     FDX_ABI_TRY
     if (!c || !P || !X || !y || n < 0) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     Pred *p = pred_of(c);
     DBuf<float> dP, dX, dy;
     int r = FDX_OK;
@@ -246,6 +248,7 @@ int fdx_mlp_grad(fdx_ctx *c, const float *P, const float *X, const float *t, int
                  float *grad, float *loss) {
     FDX_ABI_TRY
     if (!c || !P || !X || !t || !grad || n < 1) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     DBuf<float> dP, dX, dT, gp, lp, dg, dl;
     DBuf<uint32_t> di;
     auto run = [&]() -> int {
@@ -281,6 +284,7 @@ int fdx_mlp_adam(fdx_ctx *c, float *P, float *m, float *v, const float *grads, i
                  int32_t step0, double lr) {
     FDX_ABI_TRY
     if (!c || !P || !m || !v || !grads || n_steps < 0 || step0 < 0) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     if (!(std::isfinite(lr) && lr > 0)) return fail(c, FDX_EINVAL, "lr must be finite and > 0");
     DBuf<float> dP, dm, dv, dg;
     auto run = [&]() -> int {
@@ -318,6 +322,7 @@ int fdx_predictor_train(fdx_ctx *c, const float *X, const float *t, int64_t n, i
                         int32_t batch, double lr, int64_t seed, float *losses) {
     FDX_ABI_TRY
     if (!c || !X || !t || n < 16 || epochs < 1 || batch < 1) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     Pred *p = pred_of(c);
     hipStream_t s = c->stream;
     std::mt19937_64 rng((uint64_t)seed);
@@ -419,6 +424,7 @@ static const char kMagic[8] = {'F', 'D', 'X', 'M', 'L', 'P', '1', 0};
 int fdx_predictor_save(fdx_ctx *c, const char *path) {
     FDX_ABI_TRY
     if (!c || !path) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     Pred *p = pred_of(c);
     if (!p->loaded) return fail(c, FDX_ESTATE, "no predictor trained or loaded");
     std::vector<float> P(kMlpParams);
@@ -436,6 +442,7 @@ int fdx_predictor_save(fdx_ctx *c, const char *path) {
 int fdx_predictor_load(fdx_ctx *c, const char *path) {
     FDX_ABI_TRY
     if (!c || !path) return FDX_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, FDX_EHIP, "hipSetDevice failed");
     Pred *p = pred_of(c);
     FILE *f = std::fopen(path, "rb");
     if (!f) return fail(c, FDX_EINVAL, "cannot open %s", path);
