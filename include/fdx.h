@@ -54,7 +54,12 @@ typedef struct fdx_ctx fdx_ctx;
                              compensated accumulation (else FP64 kernels); a group too wide
                              for that -- 9 u min(S / eps_min, 2^d) > 1e-4 with u = 2^-24,
                              S its cell side, eps_min its smallest softening, d the depth of
-                             its deepest leaf below its cell -- is evaluated in FP64 */
+                             its deepest leaf below its cell -- is evaluated in FP64.  In large
+                             systems (above 131072 particles, large groups of one softening)
+                             superparticles beyond 64 radii of a group are summed in one
+                             polynomial about its centre and the others pair by pair; what the
+                             polynomial omits of a superparticle's force is at most about the
+                             FP32 rounding of one pair, whatever its mass */
 #define FDX_PREDICTOR 4   /* size interaction lists from the learned list-length predictor
                              (single walk; overflowing groups are re-walked exactly, so
                              forces never depend on it) */
@@ -211,10 +216,16 @@ int fdx_get_groups(fdx_ctx *ctx, uint32_t *cell, uint32_t *begin, uint32_t *coun
 
 /* Interaction lists of the last walk: n_epj[g], n_spj[g]; epj = the EPJ entries (sorted
  * particle ranks) of all groups concatenated, spj = the SPJ entries (cell ids) likewise
- * (each group's entries in the library's emission order).  Null epj and spj copy the
- * counts only. */
+ * (each group's entries in the library's emission order; after an FP32 evaluation that
+ * expanded a group's far superparticles, its near SPJ entries first).  Null epj and spj copy
+ * the counts only. */
 int fdx_get_lists(fdx_ctx *ctx, uint32_t *n_epj, uint32_t *n_spj, uint32_t *epj,
                   uint32_t *spj);
+
+/* Superparticles that the last force evaluation took pair by pair (host memory): the first
+ * n_near[g] of group g's SPJ entries; the others' field was expanded (FDX_FP32REL).
+ * n_near[g] = n_spj[g] where nothing was. */
+int fdx_get_near_counts(fdx_ctx *ctx, uint32_t *n_near);
 
 /* ---- Autotuner (n_group and force-kernel workgroup shape) ----------------------------
  * The paper finds an optimal group size from the trade-off between list construction and

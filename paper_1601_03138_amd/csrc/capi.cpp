@@ -97,10 +97,11 @@ Cells cells_view(fdx_ctx *c) {
     return v;
 }
 
-// whether the FP32 path expands far superparticles: Newtonian forces, and a system large enough
-// (the entry point that allocates nothing takes no larger one and has no buffers for it)
+// whether the FP32 path expands far superparticles: Newtonian forces, groups and a system large
+// enough (the entry point that allocates nothing takes no larger one and has no buffers for it)
 static bool use_far(const fdx_ctx *c) {
     if (!(c->flags & FDX_FP32REL) || (c->flags & FDX_FUSED) || c->cutoff > 0) return false;
+    if (c->n_group < ((c->flags & FDX_QUAD) ? kFarMinGroup : kFarMinGroupMono)) return false;
     int64_t largest = 0;
     for (int s = 0; s < c->nsys && (size_t)s + 1 < c->sys_off_h.size(); s++)
         largest = std::max(largest, c->sys_off_h[s + 1] - c->sys_off_h[s]);
@@ -176,6 +177,7 @@ int enqueue_tree_groups(fdx_ctx *c) {
 int run_tree(fdx_ctx *c, bool sync) {
     c->have_lists = false;
     c->have_counts = false;
+    c->have_near = false;
     int r = enqueue_keys_sort(c);
     if (r) return r;
     for (int attempt = 0;; attempt++) {
@@ -283,6 +285,7 @@ int enqueue_force(fdx_ctx *c, size_t gmax) {
     fa.r_cut = c->cutoff;
     fa.near = fa.fp32 && gv.far ? c->g_near.p : nullptr;
     if (fa.near) HIPCHK(c, far_expand(gmax, fa, s));
+    c->have_near = fa.near != nullptr;
     HIPCHK(c, force(gmax, fa, s));
     if (fa.fp32) {
         // groups too wide for group-relative FP32: evaluated again by the FP64 kernel, which
@@ -891,6 +894,22 @@ int fdx_get_lists(fdx_ctx *c, uint32_t *n_epj, uint32_t *n_spj, uint32_t *epj, u
         doe.release(); dos.release(); de.release(); ds.release();
         if (e != hipSuccess) return fail(c, FDX_EHIP, "get_lists: %s", hipGetErrorString(e));
     }
+    return FDX_OK;
+    FDX_ABI_CATCH(c)
+}
+
+int fdx_get_near_counts(fdx_ctx *c, uint32_t *n_near) {
+    FDX_ABI_TRY
+    if (!c || !n_near) return FDX_EINVAL;
+    if (!c->have_counts) return fail(c, FDX_ESTATE, "no walk done on the current groups");
+    const size_t G = (size_t)c->stats.n_groups;
+    std::vector<uint32_t> near(G, kNone);
+    HIPCHK(c, hipMemcpyAsync(n_near, c->cnt_s.p, 4 * G, hipMemcpyDeviceToHost, c->stream));
+    if (c->have_near)
+        HIPCHK(c, hipMemcpyAsync(near.data(), c->g_near.p, 4 * G, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (size_t g = 0; g < G; g++)
+        if (near[g] != kNone) n_near[g] = near[g];
     return FDX_OK;
     FDX_ABI_CATCH(c)
 }

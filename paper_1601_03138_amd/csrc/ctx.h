@@ -112,6 +112,7 @@ struct fdx_ctx {
     fdx::DBuf<double> ax, ay, az, pot;
     bool have_force = false;
     bool have_lists = false;       // the lists belong to the current groups (last walk)
+    bool have_near = false;        // the evaluation on them expanded far superparticles (g_near)
 
     // status
     fdx::DevStatus *st = nullptr;

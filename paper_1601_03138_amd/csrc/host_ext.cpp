@@ -206,6 +206,7 @@ int ext_integrate_graph(fdx_ctx *c, double dt, int n_steps) {
         // the replay's lists (or the eager redo's); the fused launch stores counts only
         c->have_lists = !(c->flags & FDX_FUSED);
         c->have_counts = true;
+        c->have_near = c->have_lists && groups_view(c).far;
         if (status_incomplete(h)) {
             // positions and velocities hold kick + drift; redo force and kick eagerly
             r = run_tree(c, true);

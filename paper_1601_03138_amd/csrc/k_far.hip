@@ -6,12 +6,12 @@
 // far field is evaluated and written where the force kernel adds the pairs to it.  The list is
 // partitioned in place on the way, near entries first, so the force kernel reads only those.
 //
-// About 240 instructions per far superparticle and 110 per very far one, where one pair costs
-// 34.5.  Bound by the gathers of 80-byte cell records out of L2: 2^24 clustered particles,
-// n_group 256, 6.7e8 entries, 0.40 of them far: 4.8 ms, and the force kernel 43 -> 28.3 ms on the
-// same box.  The time is the same with 2, 3 or 4 waves per SIMD, 64, 128 or 256 entries per block,
-// with a quarter fewer instructions (without the very far kind), and with records read by pairs
-// of lanes (half the L1 accesses); L2 requests are what these have in common (6.2e8).
+// About 240 instructions per far superparticle, where one pair costs 34.5.  Bound by the gathers of
+// 80-byte cell records out of L2, most of them to tell near from far: 2^24 clustered particles,
+// n_group 256, 6.7e8 entries, 0.30 of their interactions far: 4.6 ms, and the force kernel 42 -> 31.7 ms.
+// The time is the same with 2, 3 or 4 waves per SIMD, 64, 128 or 256 entries per block, with far
+// entries at half the instructions, and with records read by pairs of lanes (half the L1
+// accesses); L2 requests are what these have in common.
 #include <algorithm>
 #include <type_traits>
 
@@ -79,132 +79,11 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// accumulators: c[m][k] of far_field.h as coefficients of the monomials of r; s^k kept apart
-// (k = 1: t01, t11, t21; k = 2: t02) and multiplied out after the sum
-struct FarAcc {
-    double c0 = 0, c1[3] = {0, 0, 0};
-    float c2[6] = {}, c3[10] = {}, c4[15] = {};
-    float t01 = 0, t11[3] = {}, t21[6] = {}, t02 = 0;
-
-    template <bool QUAD, bool FOURTH>
-    __device__ __forceinline__ void add(float x, float y, float z, float M, const float (&q)[6],
-                                        float e2) {
-        const float i = __builtin_amdgcn_rsqf(fmaf(z, z, fmaf(y, y, fmaf(x, x, e2))));
-        const float i2 = i * i;
-        const float zx = x * i2, zy = y * i2, zz = z * i2;
-        const float b = M * i;
-        // quadrupole: A = X.Q.X / (2 R^5), v = Q X / R^5, h = coefficients of r.Q.r / (2 R^5)
-        float A = 0, vx = 0, vy = 0, vz = 0, h[6] = {0, 0, 0, 0, 0, 0};
-        if (QUAD) {
-            const float i5 = i * i2 * i2;
-            vx = i5 * fmaf(q[0], x, fmaf(q[3], y, q[4] * z));
-            vy = i5 * fmaf(q[3], x, fmaf(q[1], y, q[5] * z));
-            vz = i5 * fmaf(q[4], x, fmaf(q[5], y, q[2] * z));
-            A = 0.5f * fmaf(x, vx, fmaf(y, vy, z * vz));
-            const float i5h = 0.5f * i5;
-            h[0] = i5h * q[0]; h[1] = i5h * q[1]; h[2] = i5h * q[2];
-            h[3] = i5 * q[3]; h[4] = i5 * q[4]; h[5] = i5 * q[5];
-        }
-        c0 += (double)(b + A);
-        const float w1 = fmaf(5.f, A, b);
-        c1[0] += (double)fmaf(w1, zx, -vx);
-        c1[1] += (double)fmaf(w1, zy, -vy);
-        c1[2] += (double)fmaf(w1, zz, -vz);
-        // (z.r) (p.r) + d h(r): a quadratic form, added to o or returned in it
-        auto form = [&](float w, float u, float d, float (&o)[6], bool acc) {
-            const float px = fmaf(w, zx, u * vx), py = fmaf(w, zy, u * vy), pz = fmaf(w, zz, u * vz);
-            if (!QUAD) {
-                o[0] = fmaf(zx, px, acc ? o[0] : 0.f);
-                o[1] = fmaf(zy, py, acc ? o[1] : 0.f);
-                o[2] = fmaf(zz, pz, acc ? o[2] : 0.f);
-                o[3] = fmaf(zx, 2.f * py, acc ? o[3] : 0.f);
-                o[4] = fmaf(zx, 2.f * pz, acc ? o[4] : 0.f);
-                o[5] = fmaf(zy, 2.f * pz, acc ? o[5] : 0.f);
-                return;
-            }
-            o[0] = fmaf(zx, px, acc ? fmaf(d, h[0], o[0]) : d * h[0]);
-            o[1] = fmaf(zy, py, acc ? fmaf(d, h[1], o[1]) : d * h[1]);
-            o[2] = fmaf(zz, pz, acc ? fmaf(d, h[2], o[2]) : d * h[2]);
-            o[3] = fmaf(zx, py, fmaf(zy, px, acc ? fmaf(d, h[3], o[3]) : d * h[3]));
-            o[4] = fmaf(zx, pz, fmaf(zz, px, acc ? fmaf(d, h[4], o[4]) : d * h[4]));
-            o[5] = fmaf(zy, pz, fmaf(zz, py, acc ? fmaf(d, h[5], o[5]) : d * h[5]));
-        };
-        form(fmaf(17.5f, A, 1.5f * b), -5.f, 1.f, c2, true);
-        t01 = fmaf(fmaf(-2.5f, A, -0.5f * b), i2, t01);
-        // third degree: (z.r) x a quadratic form
-        float n[6];
-        form(fmaf(52.5f, A, 2.5f * b), -17.5f, 5.f, n, false);
-        c3[0] = fmaf(zx, n[0], c3[0]);
-        c3[1] = fmaf(zx, n[3], fmaf(zy, n[0], c3[1]));
-        c3[2] = fmaf(zx, n[4], fmaf(zz, n[0], c3[2]));
-        c3[3] = fmaf(zx, n[1], fmaf(zy, n[3], c3[3]));
-        c3[4] = fmaf(zx, n[5], fmaf(zy, n[4], fmaf(zz, n[3], c3[4])));
-        c3[5] = fmaf(zx, n[2], fmaf(zz, n[4], c3[5]));
-        c3[6] = fmaf(zy, n[1], c3[6]);
-        c3[7] = fmaf(zy, n[5], fmaf(zz, n[1], c3[7]));
-        c3[8] = fmaf(zy, n[2], fmaf(zz, n[5], c3[8]));
-        c3[9] = fmaf(zz, n[2], c3[9]);
-        const float w11 = fmaf(-17.5f, A, -1.5f * b);
-        t11[0] = fmaf(i2, fmaf(w11, zx, 2.5f * vx), t11[0]);
-        t11[1] = fmaf(i2, fmaf(w11, zy, 2.5f * vy), t11[1]);
-        t11[2] = fmaf(i2, fmaf(w11, zz, 2.5f * vz), t11[2]);
-        if (!FOURTH) return;
-        // fourth degree: (z.r)^2 x a quadratic form, by way of the cubic (z.r) x the form
-        form(fmaf(144.375f, A, 4.375f * b), -52.5f, 17.5f, n, false);
-        float k[10];
-        k[0] = zx * n[0];
-        k[1] = fmaf(zx, n[3], zy * n[0]);
-        k[2] = fmaf(zx, n[4], zz * n[0]);
-        k[3] = fmaf(zx, n[1], zy * n[3]);
-        k[4] = fmaf(zx, n[5], fmaf(zy, n[4], zz * n[3]));
-        k[5] = fmaf(zx, n[2], zz * n[4]);
-        k[6] = zy * n[1];
-        k[7] = fmaf(zy, n[5], zz * n[1]);
-        k[8] = fmaf(zy, n[2], zz * n[5]);
-        k[9] = zz * n[2];
-        c4[0] = fmaf(zx, k[0], c4[0]);
-        c4[1] = fmaf(zx, k[1], fmaf(zy, k[0], c4[1]));
-        c4[2] = fmaf(zx, k[2], fmaf(zz, k[0], c4[2]));
-        c4[3] = fmaf(zx, k[3], fmaf(zy, k[1], c4[3]));
-        c4[4] = fmaf(zx, k[4], fmaf(zy, k[2], fmaf(zz, k[1], c4[4])));
-        c4[5] = fmaf(zx, k[5], fmaf(zz, k[2], c4[5]));
-        c4[6] = fmaf(zx, k[6], fmaf(zy, k[3], c4[6]));
-        c4[7] = fmaf(zx, k[7], fmaf(zy, k[4], fmaf(zz, k[3], c4[7])));
-        c4[8] = fmaf(zx, k[8], fmaf(zy, k[5], fmaf(zz, k[4], c4[8])));
-        c4[9] = fmaf(zx, k[9], fmaf(zz, k[5], c4[9]));
-        c4[10] = fmaf(zy, k[6], c4[10]);
-        c4[11] = fmaf(zy, k[7], fmaf(zz, k[6], c4[11]));
-        c4[12] = fmaf(zy, k[8], fmaf(zz, k[7], c4[12]));
-        c4[13] = fmaf(zy, k[9], fmaf(zz, k[8], c4[13]));
-        c4[14] = fmaf(zz, k[9], c4[14]);
-        form(fmaf(-78.75f, A, -3.75f * b), 17.5f, -2.5f, n, false);
-#pragma unroll
-        for (int u = 0; u < 6; u++) t21[u] = fmaf(i2, n[u], t21[u]);
-        t02 = fmaf(fmaf(4.375f, A, 0.375f * b), i2 * i2, t02);
-    }
-
-    // multiply the powers of r^2 out into the monomials
-    __device__ __forceinline__ void fold() {
-#pragma unroll
-        for (int u = 0; u < 3; u++) c2[u] += t01;
-        c3[0] += t11[0]; c3[3] += t11[0]; c3[5] += t11[0];
-        c3[1] += t11[1]; c3[6] += t11[1]; c3[8] += t11[1];
-        c3[2] += t11[2]; c3[7] += t11[2]; c3[9] += t11[2];
-        c4[0] += t21[0] + t02; c4[10] += t21[1] + t02; c4[14] += t21[2] + t02;
-        c4[3] += t21[0] + t21[1] + 2.f * t02;
-        c4[5] += t21[0] + t21[2] + 2.f * t02;
-        c4[12] += t21[1] + t21[2] + 2.f * t02;
-        c4[1] += t21[3]; c4[6] += t21[3]; c4[8] += t21[3];
-        c4[2] += t21[4]; c4[7] += t21[4]; c4[9] += t21[4];
-        c4[4] += t21[5]; c4[11] += t21[5]; c4[13] += t21[5];
-    }
-};
-
 template <bool QUAD>
 __global__ void __launch_bounds__(kThreads, 3)
 k_far(FarArgs a) {
-    __shared__ float4 qx_all[kWaves][2][kQueue];       // to be expanded: far, very far
-    __shared__ uint32_t qi_all[QUAD ? kWaves : 1][2][QUAD ? kQueue : 1];
+    __shared__ float4 qx_all[kWaves][kQueue];          // to be expanded
+    __shared__ uint32_t qi_all[QUAD ? kWaves : 1][QUAD ? kQueue : 1];
     __shared__ uint32_t held_all[kWaves][2][kHeld];    // ids to be written back: near, far
     const int w = threadIdx.x / kWave, lane = lane_id();
     const uint64_t lt = lanemask_lt();
@@ -226,21 +105,19 @@ k_far(FarArgs a) {
     const double q2 = f.inv_h * f.inv_h;
     FarAcc acc;
     const float inv_h = (float)f.inv_h;            // a power of two: scaling by it is exact
-    const float thr2 = f.thr2, thr3 = f.thr2 * ((kFar3Ratio / kFarRatio) * (kFar3Ratio / kFarRatio));
-    auto expand = [&](auto fourth, uint32_t slot) {
-        constexpr bool FOURTH = decltype(fourth)::value;
-        const float4 e = qx_all[w][FOURTH ? 0 : 1][slot];
+    auto expand = [&](uint32_t slot) {
+        const float4 e = qx_all[w][slot];
         float q[6] = {0, 0, 0, 0, 0, 0};
         if (QUAD) {
-            const double2 *o = mom + 5 * (size_t)qi_all[w][FOURTH ? 0 : 1][slot] + 2;
+            const double2 *o = mom + 5 * (size_t)qi_all[w][slot] + 2;
             const double2 u = o[0], v = o[1], t = o[2];
             q[0] = (float)(u.x * q2); q[1] = (float)(u.y * q2); q[2] = (float)(v.x * q2);
             q[3] = (float)(v.y * q2); q[4] = (float)(t.x * q2); q[5] = (float)(t.y * q2);
         }
-        acc.template add<QUAD, FOURTH>(e.x * inv_h, e.y * inv_h, e.z * inv_h, e.w, q, f.e2);
+        const float x = e.x * inv_h, y = e.y * inv_h, z = e.z * inv_h;
+        const float i = __builtin_amdgcn_rsqf(fmaf(z, z, fmaf(y, y, fmaf(x, x, f.e2))));
+        acc.template add<QUAD>(x, y, z, i, e.w, q);
     };
-    constexpr std::true_type all{};                // far: to the fourth degree
-    constexpr std::false_type third{};             // very far: to the third
     // The list is partitioned in place, near entries from its front and far ones from its back,
     // in blocks that are read ahead from either end.  Entries read and not yet written back are
     // as many as the slots read and not yet overwritten; after each block as many ids as have a
@@ -271,7 +148,7 @@ k_far(FarArgs a) {
             v[k] = mom[5 * (size_t)id[k] + 1];
         }
     };
-    uint32_t cnt[2] = {0, 0};                      // queued for expansion, the same in every lane
+    uint32_t cnt = 0;                              // queued for expansion, the same in every lane
     Block b0 = choose(0), b1 = choose(0);
     uint32_t id0[kScan], id1[kScan];
     double2 u0[kScan], v0[kScan];
@@ -285,10 +162,9 @@ k_far(FarArgs a) {
                         pz = (float)(v0[k].y - f.ez);
             const float r2 = fmaf(pz, pz, fmaf(py, py, px * px));
             const bool in = (uint32_t)(k * kWave + lane) < b0.len;
-            const bool far = r2 > thr2 && in, far3 = r2 > thr3 && in;
-            const uint64_t m = __ballot(far), m3 = __ballot(far3);
-            const uint32_t nf = (uint32_t)__popcll(m), n3 = (uint32_t)__popcll(m3);
-            const uint32_t rank = (uint32_t)__popcll(m & lt), rank3 = (uint32_t)__popcll(m3 & lt);
+            const bool far = r2 > f.thr2 && in;
+            const uint64_t m = __ballot(far);
+            const uint32_t nf = (uint32_t)__popcll(m), rank = (uint32_t)__popcll(m & lt);
             if (in) {
                 // the entries of a block are its first lanes, so the near ones before a lane are
                 // the lanes before it less the far ones
@@ -296,13 +172,10 @@ k_far(FarArgs a) {
                     id0[k];
             }
             if (far) {
-                const uint32_t c = far3 ? 1u : 0u;
-                const uint32_t s = far3 ? cnt[1] + rank3 : cnt[0] + rank - rank3;
-                qx_all[w][c][s] = make_float4(px, py, pz, (float)u0[k].x);
-                if (QUAD) qi_all[w][c][s] = id0[k];
+                qx_all[w][cnt + rank] = make_float4(px, py, pz, (float)u0[k].x);
+                if (QUAD) qi_all[w][cnt + rank] = id0[k];
             }
-            cnt[0] += nf - n3;
-            cnt[1] += n3;
+            cnt += nf;
             held[0] += min(kWave + 0u, b0.len > (uint32_t)(k * kWave) ? b0.len - k * kWave : 0u) - nf;
             held[1] += nf;
         }
@@ -328,13 +201,9 @@ k_far(FarArgs a) {
             put[c] += n;
             room[c] -= n;
         }
-        while (cnt[0] >= (uint32_t)kWave) {
-            cnt[0] -= kWave;
-            expand(all, cnt[0] + (uint32_t)lane);
-        }
-        while (cnt[1] >= (uint32_t)kWave) {
-            cnt[1] -= kWave;
-            expand(third, cnt[1] + (uint32_t)lane);
+        while (cnt >= (uint32_t)kWave) {
+            cnt -= kWave;
+            expand(cnt + (uint32_t)lane);
         }
         wave_barrier();
     }
@@ -346,8 +215,7 @@ k_far(FarArgs a) {
             spj[slot] = held_all[w][c][i];
         }
     if (lane == 0) a.near[gi] = put[0] + held[0];
-    if ((uint32_t)lane < cnt[0]) expand(all, (uint32_t)lane);
-    if ((uint32_t)lane < cnt[1]) expand(third, (uint32_t)lane);
+    if ((uint32_t)lane < cnt) expand((uint32_t)lane);
     acc.fold();
     // the sums over the wave, the same in every lane
     FarCoef c;

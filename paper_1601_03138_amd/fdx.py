@@ -33,7 +33,8 @@ EXPORTS = ["fdx_create", "fdx_destroy", "fdx_set_particles", "fdx_build_tree", "
            "fdx_calc_force_cutoff", "fdx_dd_factor", "fdx_decompose", "fdx_get_decomposition",
            "fdx_get_dd_samples", "fdx_get_dd_destinations", "fdx_exchange_particles",
            "fdx_get_dd_stats", "fdx_direct_forces", "fdx_autotune_cached",
-           "fdx_set_graph_list_margin", "fdx_calc_force_noalloc", "fdx_set_list_capture"]
+           "fdx_set_graph_list_margin", "fdx_calc_force_noalloc", "fdx_set_list_capture",
+           "fdx_get_near_counts"]
 
 
 class FdxError(RuntimeError):
@@ -111,6 +112,7 @@ def _declare(L):
     L.fdx_get_tree.argtypes = [vp] + [vp] * 11
     L.fdx_get_groups.argtypes = [vp] + [vp] * 6
     L.fdx_get_lists.argtypes = [vp] + [vp] * 4
+    L.fdx_get_near_counts.argtypes = [vp, vp]
     L.fdx_last_error.argtypes = [vp]
     L.fdx_last_error.restype = C.c_char_p
     L.fdx_autotune_shapes.argtypes = []
@@ -316,6 +318,12 @@ class Context:
         self._check(self.lib.fdx_get_lists(self.h, _ptr(ne), _ptr(ns), _ptr(epj), _ptr(spj)),
                     "get_lists")
         return ne, ns, epj[:int(st["n_epj"])], spj[:int(st["n_spj"])]
+
+    def near_counts(self):
+        """Superparticles of each group that the last evaluation took pair by pair."""
+        n = np.empty(int(self.stats()["n_groups"]), np.uint32)
+        self._check(self.lib.fdx_get_near_counts(self.h, _ptr(n)), "get_near_counts")
+        return n
 
     # -- autotuner ---------------------------------------------------------------------
     def autotune(self, theta, n_leaf, eps, flags, n_group_candidates, reps=2):
