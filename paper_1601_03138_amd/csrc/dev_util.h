@@ -6,6 +6,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "group_items.h"
+
 namespace fdx {
 
 constexpr int kWave = 64;
@@ -241,25 +243,6 @@ __device__ __forceinline__ void wave_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Order of blocks of neighbouring groups over the 8 XCDs: blocks go to the XCDs in turn, and the
-// blocks of one XCD take runs of kXcdRun consecutive blocks of groups, so groups near each other,
-// whose lists overlap, are worked on behind one L2, while every XCD still gets dense and sparse
-// regions.  Grids are multiples of 8 kXcdRun, or the whole of it.
-constexpr uint32_t kXcdRun = 64;
-__host__ __device__ inline uint32_t xcd_run_blocks(size_t blocks, uint32_t run = kXcdRun) {
-    return (uint32_t)((blocks + 8 * run - 1) / (8 * run) * (8 * run));
-}
-__device__ __forceinline__ uint32_t xcd_run_block(uint32_t vb, uint32_t run = kXcdRun) {
-    const uint32_t nb = vb / 8u;
-    return (nb / run * 8u + vb % 8u) * run + nb % run;
-}
-// run for a launch of one block per group: at most `most`, and every XCD gets 16 runs or more
-inline uint32_t xcd_direct_run(size_t blocks, uint32_t most) {
-    uint32_t r = most;
-    while (r > 1 && 8 * 16 * (size_t)r > blocks) r >>= 1;
-    return r;
 }
 
 // Grid-stride index helpers.

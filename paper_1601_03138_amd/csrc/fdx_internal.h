@@ -218,7 +218,7 @@ hipError_t sph_cell_hmax(size_t n, int nsys, const int64_t *sys_off, const uint3
                          const Cells c, const double *sh, double *hmax, hipStream_t s);
 hipError_t sph_group_hmax(size_t gmax, const Groups g, const double *sh, double *rg,
                           DevStatus *st, hipStream_t s);
-hipError_t sph_density(int mode, size_t gmax, const Groups g, const uint64_t *seg,
+hipError_t sph_density(int mode, size_t gmax, int n_group, const Groups g, const uint64_t *seg,
                        const uint32_t *cnt_e, const uint32_t *list, const double4 *jp,
                        const double *sh, double *rho_s, uint32_t *n_s, DevStatus *st,
                        hipStream_t s);

@@ -12,8 +12,8 @@
 // simulation"; Dehnen & Aly 2012), q = r / H < 1:
 //   W(r, H) = 1365 / (64 pi H^3) (1 - q)^8 (1 + 8 q + 25 q^2 + 32 q^3).
 // |r_ij|^2 = dx*dx + dy*dy + dz*dz is rounded as written (no contraction) and compared with
-// H*H, so which pairs count is exact.  FP64 throughout; one workgroup per group, candidate
-// tiles staged in LDS, per-slice partial sums combined in slice order (deterministic).
+// H*H, so which pairs count is exact.  FP64 throughout; a wave takes runs of a group's members and
+// the candidates near them, partial sums combined in a fixed order (deterministic).
 #include "bottom_up.h"
 #include "dev_util.h"
 #include "fdx_internal.h"
@@ -110,10 +110,11 @@ struct DensArgs {
     const double *sh;
     double *rho;
     uint32_t *nngb;
+    uint32_t parts, run;          // waves per group; consecutive blocks per XCD
 };
 
-// One wave per group, so nothing waits for other waves (half of the particles of a uniform set
-// sit in groups of about eight).  The members are taken in runs of up to 16, neighbours along the
+// One wave per group, or several where groups are few (group_items.h), so nothing waits for other waves
+// (half of the particles of a uniform set sit in groups of about eight).  The members are taken in runs of up to 16, neighbours along the
 // curve; for each run the wave reads the candidates 64 at a time, keeps those within reach of
 // the run's box in LDS (farther ones lie outside every support radius that could make a pair
 // count), and lets the kept ones meet the run, js at a time.  FP64 VALU bound: 9 instructions
@@ -121,7 +122,6 @@ struct DensArgs {
 // one).  2^24 uniform particles, 306 neighbours, 1540 candidates per member: 25.0 -> 18.6 ms
 // (0.86 of the cycles issue a VALU instruction); runs of up to 8, 12, 20 members: 19.4, 18.7, 18.6 ms;
 // a workgroup per group with the tile sifted by four waves: 24.0 ms, waiting at barriers.
-constexpr uint32_t kRunMax = 16;
 constexpr uint32_t kHold = 2 * kWave;      // a block of 64 on top of up to 64 kept
 
 template <int MODE>   // 0 fixed, 1 scatter, 2 gather, 3 symmetric
@@ -136,16 +136,17 @@ __global__ void __launch_bounds__(kSiftThreads) k_density(DensArgs a) {
     const uint64_t lt = lanemask_lt();
     double4 *kept = kept_all[w];
     double3 *kepth = kepth_all[HJ ? w : 0];
-    const uint32_t vblocks = xcd_run_blocks((G + kSiftWaves - 1) / kSiftWaves);
+    const uint32_t vblocks = xcd_run_blocks(((size_t)G * a.parts + kSiftWaves - 1) / kSiftWaves, a.run);
     for (uint32_t vb = blockIdx.x; vb < vblocks; vb += gridDim.x) {
-        const uint32_t gi = uniform_u32(xcd_run_block(vb) * kSiftWaves + w);
-        if (gi >= G) continue;
+        const uint32_t item = uniform_u32(xcd_run_block(vb, a.run) * kSiftWaves + w);
+        const uint32_t part = item / G, gi = item - part * G;
+        if (part >= a.parts) continue;
         const uint32_t gb = uniform_u32(a.gbegin[gi]), ni = uniform_u32(a.gcount[gi]),
                        ne = uniform_u32(a.cnt_e[gi]);
         const uint32_t *cand = a.list + uniform_u64(a.seg[gi]);
         const uint32_t nrun = (ni + kRunMax - 1) / kRunMax, bs = (ni + nrun - 1) / nrun;
         const uint32_t js = kWave / bs, slot = lane / bs;
-        for (uint32_t r0 = 0; r0 < ni; r0 += bs) {
+        for (uint32_t r0 = part * bs; r0 < ni; r0 += bs * a.parts) {
             const uint32_t n = min(bs, ni - r0), li = lane % bs;
             const bool active = slot < js && li < n;
             const uint32_t i = gb + r0 + (active ? li : 0u);
@@ -291,14 +292,14 @@ hipError_t sph_group_hmax(size_t gmax, const Groups g, const double *sh, double 
     return hipGetLastError();
 }
 
-hipError_t sph_density(int mode, size_t gmax, const Groups g, const uint64_t *seg,
+hipError_t sph_density(int mode, size_t gmax, int n_group, const Groups g, const uint64_t *seg,
                        const uint32_t *cnt_e, const uint32_t *list, const double4 *jp,
                        const double *sh, double *rho_s, uint32_t *n_s, DevStatus *st,
                        hipStream_t s) {
     if (!gmax) return hipSuccess;
-    DensArgs a{&st->n_groups_c, g.begin, g.count, seg, cnt_e, list, jp, sh, rho_s, n_s};
-    const size_t blocks = xcd_run_blocks((gmax + kSiftWaves - 1) / kSiftWaves);
-    const unsigned grid = (unsigned)(blocks < 65536 ? blocks : 65536);   // 8 kXcdRun divides both
+    const GroupItems o = density_items(gmax, n_group);
+    DensArgs a{&st->n_groups_c, g.begin, g.count, seg, cnt_e, list, jp, sh, rho_s, n_s, o.parts, o.run};
+    const unsigned grid = o.blocks < 65536 ? o.blocks : 65536;   // 8 o.run divides both
     switch (mode) {
         case 0: hipLaunchKernelGGL(k_density<0>, dim3(grid), dim3(kSiftThreads), 0, s, a); break;
         case 1: hipLaunchKernelGGL(k_density<1>, dim3(grid), dim3(kSiftThreads), 0, s, a); break;

@@ -118,7 +118,7 @@ int fdx_calc_density(fdx_ctx *c, int32_t mode, double r_cut, const double *h, in
     c->stats.overflow_groups = 0;
     HIPCHK(c, list_stats(G, gv, c->cnt_e.p, c->cnt_s.p, c->st, s));
     mark(c, 6);
-    HIPCHK(c, sph_density(mode, G, gv, c->seg.p, c->cnt_e.p, c->list.p, c->jp.p, x->sh.p,
+    HIPCHK(c, sph_density(mode, G, c->n_group, gv, c->seg.p, c->cnt_e.p, c->list.p, c->jp.p, x->sh.p,
                           x->rho_s.p, x->n_s.p, c->st, s));
     mark(c, 7);
     HIPCHK(c, sph_unsort(n, c->inv.p, x->rho_s.p, x->n_s.p, x->rho.p, x->nngb.p, s));

@@ -1,0 +1,29 @@
+"""Groups whose runs of members are shared out over several waves or workgroups: the density does not
+depend on how."""
+import numpy as np
+import pytest
+
+from paper_1601_03138_amd import fdx
+from paper_1601_03138_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# 16: one run and one wave per group; 64, 200, 512: up to 4, 13 and 32 runs over as many waves as
+# 16384 items allow (all of them for the small set, some for the large one)
+@pytest.mark.parametrize("n", [3001, 120001])
+@pytest.mark.parametrize("mode", [fdx.CUT_FIXED, fdx.CUT_SYMMETRIC])
+def test_density_does_not_depend_on_the_split(n, mode):
+    ps = I.uniform_cube(n, 5, 1e-3)
+    k = 4.2 * n ** (-1.0 / 3.0)
+    h = None if mode == fdx.CUT_FIXED else k * np.random.default_rng(6).uniform(0.9, 1.1, n)
+    out = []
+    with fdx.Context(0) as ctx:
+        ctx.set_particles(ps)
+        for n_group in (16, 64, 200, 512):
+            ctx.calc_density(mode, k if h is None else 0.0, h, 8, n_group)
+            out.append(ctx.density())
+    for rho, ngb in out[1:]:
+        assert np.array_equal(ngb, out[0][1])
+        # sums of about 300 positive terms in another order: 300 x 2^-53
+        assert np.max(np.abs(rho / out[0][0] - 1)) < 1e-13
