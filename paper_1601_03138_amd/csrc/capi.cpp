@@ -283,6 +283,7 @@ int enqueue_force(fdx_ctx *c, size_t gmax) {
     fa.bounds = persistent ? c->f_bounds.p : nullptr;
     fa.variant = ext_force_variant(c);
     fa.r_cut = c->cutoff;
+    fa.n_group = c->n_group;
     fa.near = fa.fp32 && gv.far ? c->g_near.p : nullptr;
     if (fa.near) HIPCHK(c, far_expand(gmax, fa, s));
     c->have_near = fa.near != nullptr;

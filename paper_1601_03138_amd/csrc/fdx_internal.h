@@ -327,6 +327,7 @@ struct ForceArgs {
     DevStatus *st;
     bool quad, fp32, persistent;
     int variant;            // kernel shape chosen by the autotuner
+    int n_group = kMaxGroup;           // bounds the members of a group
     double r_cut = 0.0;     // > 0: tree part of TreePM (monopole, S2 cutoff), no potential
     const uint32_t *count = nullptr;   // persistent launch: device group count (default: all)
     uint32_t *near = nullptr;          // FP32: far superparticles come from far_expand, which

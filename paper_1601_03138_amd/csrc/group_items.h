@@ -55,14 +55,24 @@ inline GroupItems group_items(size_t groups, uint32_t most, size_t want, uint32_
 }
 
 // Density: a wave takes runs of up to kRunMax members.  It needs several waves on every SIMD, and the
-// groups of a small set, or large groups, are too few: 2e5 uniform particles, 4.2 spacings, n_group
-// 512, a wave per group 2.30 ms, 16384 items 0.85; 20000 particles, 7 spacings, n_group 64, 0.87 and
-// 0.25.  Items 4096 / 8192 / 16384 / 32768: 140 calls of 500 to 10^6 particles, 0.48 / 0.47 / 0.47 / 0.47
-// of the time that a workgroup per group took.
+// groups of a small set, or large groups, are too few.  Whole call of 2e5 uniform particles, 4.2
+// spacings, n_group 512: a wave per group 2.30 ms, 16384 items 0.67; 20000 particles, 7 spacings, n_group
+// 64: 0.86 and 0.46; n_group 512: 3.57 and 0.57.  140 calls of 500 to 10^6 particles with 4096 / 8192 /
+// 16384 / 32768 items: 0.48 / 0.47 / 0.47 / 0.47 of the time that a workgroup per group took.
 constexpr uint32_t kRunMax = 16;
 constexpr size_t kDensityItems = 16384;
 inline GroupItems density_items(size_t groups, int n_group) {
     return group_items(groups, ((uint32_t)n_group + kRunMax - 1) / kRunMax, kDensityItems, 4, kXcdRun);
+}
+
+// Cutoff force: a workgroup takes a pass of up to kSiftPass members, all passes of a group unless
+// groups are few.  3e5 uniform particles, n_group 512 (770 groups), FP32, cutoff of 6 spacings: 1.21 ms
+// with a workgroup per group, 1.04 / 0.93 / 0.89 with 4096 / 8192 / 16384 items.
+constexpr uint32_t kSiftPass = 80;        // 20 members per wave, three entries at a time
+constexpr size_t kCutItems = 16384;
+FDX_ITEMS_HD inline uint32_t sift_passes(uint32_t ni) { return (ni + kSiftPass - 1) / kSiftPass; }
+inline GroupItems cut_items(size_t groups, int n_group) {
+    return group_items(groups, sift_passes((uint32_t)n_group), kCutItems, 1, kXcdRun);
 }
 
 }  // namespace fdx

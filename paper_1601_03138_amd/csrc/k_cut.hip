@@ -5,7 +5,7 @@
 // factor only, no potential.  Particles and superparticles (monopole at the centre of mass) have
 // the same pair term, so both lists run through one loop.
 //
-// One workgroup evaluates one group: entries are staged 256 at a time in LDS, every wave sifts
+// One workgroup evaluates one group, or some of its passes: entries are staged 256 at a time in LDS, every wave sifts
 // the tile for its run of members (sift.h) and evaluates what it kept.  A dropped entry lies
 // beyond r_cut of every member of the run, where g = 0.  VALU bound.  2^24 uniform particles,
 // r_cut three mesh widths, groups of 64 (976 entries per member, 113 particles within the
@@ -37,7 +37,8 @@ struct CutArgs {
     const uint32_t *cap, *cnt_e, *cnt_s, *list, *order, *bounds, *ngroups;
     double4 *fs;
     DevStatus *st;
-    uint32_t G, run;
+    uint32_t G;
+    GroupItems items;         // direct launch
     double r_cut;
 };
 
@@ -87,7 +88,8 @@ struct CutSmem {
 };
 
 template <class T>
-__device__ __forceinline__ void cut_group(const CutArgs &a, uint32_t gi, CutSmem<T> &sm) {
+__device__ __forceinline__ void cut_group(const CutArgs &a, uint32_t gi, uint32_t part, uint32_t parts,
+                                          CutSmem<T> &sm) {
     using V = typename V4<T>::t;
     const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id();
     const int w = (int)(tid / kWave);
@@ -110,7 +112,7 @@ __device__ __forceinline__ void cut_group(const CutArgs &a, uint32_t gi, CutSmem
         const double *o = a.mom + 10 * (size_t)spj[k - ne];
         return make_double4(o[1], o[2], o[3], o[0]);
     };
-    for (uint32_t pass = 0; pass < SiftMap::passes(ni); pass++) {
+    for (uint32_t pass = part; pass < sift_passes(ni); pass += parts) {
         const SiftMap m(ni, pass);
         const uint32_t r = gb + m.first + (m.active ? m.member : 0u);
         const double4 p = a.jp[r];
@@ -180,9 +182,10 @@ template <class T>
 __global__ void __launch_bounds__(kSiftThreads) k_cut_direct(CutArgs a) {
     __shared__ CutSmem<T> sm;
     // XCD-aware order, as the Newtonian kernels'
-    const uint32_t q = xcd_run_block(blockIdx.x, a.run);
-    if (q >= a.G) return;
-    cut_group<T>(a, a.order ? a.order[q] : q, sm);
+    const uint32_t item = xcd_run_block(blockIdx.x, a.items.run);
+    const uint32_t part = item / a.G, q = item - part * a.G;
+    if (part >= a.items.parts) return;
+    cut_group<T>(a, a.order ? a.order[q] : q, part, a.items.parts, sm);
 }
 
 template <class T>
@@ -198,7 +201,7 @@ __global__ void __launch_bounds__(kSiftThreads) k_cut_persistent(CutArgs a) {
         const uint32_t slot = sm.slot;
         __syncthreads();
         if (slot >= G) break;
-        cut_group<T>(a, a.order ? a.order[slot] : slot, sm);
+        cut_group<T>(a, a.order ? a.order[slot] : slot, 0, 1, sm);
     }
 }
 
@@ -206,8 +209,7 @@ template <class T>
 hipError_t launch(const CutArgs &a, bool persistent, hipStream_t s) {
     if (!persistent) {
         if (!a.G) return hipSuccess;
-        hipLaunchKernelGGL(k_cut_direct<T>, dim3(xcd_run_blocks(a.G, a.run)),
-                           dim3(kSiftThreads), 0, s, a);
+        hipLaunchKernelGGL(k_cut_direct<T>, dim3(a.items.blocks), dim3(kSiftThreads), 0, s, a);
         return hipGetLastError();
     }
     int dev = 0, ncu = 256, per_cu = 0;
@@ -231,8 +233,12 @@ hipError_t cut_force(size_t G, const ForceArgs &fa, hipStream_t s) {
     a.order = fa.order; a.bounds = fa.bounds;
     a.ngroups = fa.count ? fa.count : &fa.st->n_groups_c;
     a.fs = fa.fs; a.st = fa.st; a.G = (uint32_t)G; a.r_cut = fa.r_cut;
-    a.run = xcd_direct_run(G, 64);        // 2^23 uniform: 64 3.30 ms, 16 3.41
-    return fa.fp32 ? launch<float>(a, fa.persistent, s) : launch<double>(a, fa.persistent, s);
+    a.items = cut_items(G, fa.n_group);   // runs of 64 blocks per XCD, 2^23 uniform: 3.30 ms, of 16 3.41
+    // Few groups of many passes are left to the direct launch, which splits them, unless they are a list
+    // of unknown length: 3e5 particles, n_group 512, FP32: 1.46 ms persistent, 0.89 direct.  With two
+    // parts the queues' balance is worth more (10^6, n_group 256, FP64: 6.16 and 6.53).
+    const bool persistent = fa.persistent && (fa.order || a.items.parts <= 2);
+    return fa.fp32 ? launch<float>(a, persistent, s) : launch<double>(a, persistent, s);
 }
 
 }  // namespace fdx

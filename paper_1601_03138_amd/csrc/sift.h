@@ -13,7 +13,6 @@ namespace fdx {
 
 constexpr int kSiftThreads = 256;
 constexpr int kSiftWaves = kSiftThreads / kWave;
-constexpr uint32_t kSiftPass = 80;        // members per pass: 20 per wave, three entries at a time
 
 // Mapping of a workgroup of four waves (TreePM): every wave has one run, or, in small groups, a
 // run and a part of the entries.  Members [first, first + n) of a group in this pass, cut into
@@ -36,9 +35,6 @@ struct SiftMap {
         slot = lane / bs;
         member = sub * bs + lane % bs;
         active = slot < js && member < n;
-    }
-    static __device__ __forceinline__ uint32_t passes(uint32_t ni) {
-        return (ni + kSiftPass - 1) / kSiftPass;
     }
     // thread holding the partial sum of member i of the pass from part p, slot s
     __device__ __forceinline__ uint32_t thread_of(uint32_t i, uint32_t p, uint32_t s) const {

@@ -33,7 +33,9 @@ static void check(const char *name, size_t groups, int n_group, const GroupItems
 int main() {
     for (size_t groups : {1ul, 2ul, 7ul, 33ul, 130ul, 511ul, 512ul, 1000ul, 4097ul, 16383ul, 16384ul,
                           16385ul, 70001ul, 300000ul})
-        for (int n_group : {1, 8, 16, 17, 64, 80, 81, 100, 128, 256, 512})
+        for (int n_group : {1, 8, 16, 17, 64, 80, 81, 100, 128, 256, 512}) {
             check("density", groups, n_group, density_items(groups, n_group), 4);
+            check("cut", groups, n_group, cut_items(groups, n_group), 1);
+        }
     return 0;
 }

@@ -1,5 +1,5 @@
-"""Groups whose runs of members are shared out over several waves or workgroups: the density does not
-depend on how."""
+"""Groups whose runs or passes of members are shared out over several waves or workgroups: density and
+cutoff force do not depend on how."""
 import numpy as np
 import pytest
 
@@ -27,3 +27,19 @@ def test_density_does_not_depend_on_the_split(n, mode):
         assert np.array_equal(ngb, out[0][1])
         # sums of about 300 positive terms in another order: 300 x 2^-53
         assert np.max(np.abs(rho / out[0][0] - 1)) < 1e-13
+
+
+# 4000 to 16000 groups of up to two passes: the direct launch splits them, the persistent one does not
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("n,n_group", [(400009, 100), (400009, 160), (250007, 81)])
+def test_cutoff_force_does_not_depend_on_the_split(n, n_group, fp32):
+    ps = I.uniform_cube(n, 7, 1e-3)
+    with fdx.Context(0) as ctx:
+        ctx.set_particles(ps)
+        ctx.calc_force_cutoff(0.5, 8, n_group, 0.0, 3.0 * n ** (-1.0 / 3.0), fp32=fp32)
+        groups = int(ctx.stats()["n_groups"])
+        assert groups < 16384 and (ctx.groups()["count"] > 80).any()
+        direct = ctx.forces()
+        ctx.calc_force_cutoff(0.5, 8, n_group, 0.0, 3.0 * n ** (-1.0 / 3.0), fp32=fp32,
+                              persistent=True)
+        assert np.array_equal(direct, ctx.forces())

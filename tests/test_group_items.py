@@ -9,7 +9,8 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1601_03138_amd", "csrc")
-ITEMS = {"density": (16384, lambda n_group: -(-n_group // 16))}
+ITEMS = {"density": (16384, lambda n_group: -(-n_group // 16)),
+         "cut": (16384, lambda n_group: -(-n_group // 80))}
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
