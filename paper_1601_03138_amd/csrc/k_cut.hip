@@ -14,7 +14,7 @@
 // by up to 6.6e-6; now 3e-7).
 //
 // FP32: positions relative to the centre of the group's cell; each tile's sum is added to a
-// compensated accumulator.  FP64: the same in FP64 with the correctly rounded square root.
+// compensated accumulator.  FP64: the same in FP64.
 #include "dev_util.h"
 #include "fdx_internal.h"
 #include "group_queue.h"
@@ -58,7 +58,9 @@ __device__ __forceinline__ T s2_cutoff(T xi) {
     return fma(s6, t, u5 * p);
 }
 __device__ __forceinline__ float cut_dist(float r2) { return __builtin_amdgcn_sqrtf(r2); }
-__device__ __forceinline__ double cut_dist(double r2) { return sqrt(r2); }
+// (coincident points get 1e-145.)  10^6 uniform particles, n_group 256, FP64, cutoff of 3 spacings: 2.28 ms
+// with the general sqrt, 2.05 with this one.
+__device__ __forceinline__ double cut_dist(double r2) { return sqrt_pos(r2 + 1e-290); }
 
 // Kahan accumulator (FP32) or plain sum (FP64)
 template <class T> struct Acc {

