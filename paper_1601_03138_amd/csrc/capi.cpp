@@ -97,8 +97,9 @@ Cells cells_view(fdx_ctx *c) {
     return v;
 }
 
-// whether the FP32 path expands far superparticles: Newtonian forces, groups and a system large
-// enough (the entry point that allocates nothing takes no larger one and has no buffers for it)
+// whether the FP32 path may expand far superparticles: Newtonian forces, groups and a system large
+// enough (the entry point that allocates nothing takes no larger one and has no buffers for it);
+// which groups of which systems, the groups' geometry says
 static bool use_far(const fdx_ctx *c) {
     if (!(c->flags & FDX_FP32REL) || (c->flags & FDX_FUSED) || c->cutoff > 0) return false;
     if (c->n_group < ((c->flags & FDX_QUAD) ? kFarMinGroup : kFarMinGroupMono)) return false;

@@ -55,8 +55,11 @@ constexpr float kFarSpan = 8.0f;
 // Plummer 2.30 and 2.09; 100: 8e6 clustered 18.9 and 19.8.  Monopole pairs cost less than half as
 // much: 64: 2e6 Plummer 2.74 and 2.56; 128: 8e6 clustered 11.29 and 11.10; 512: 3e6 2.27 and 2.30.
 constexpr int kFarMinGroup = 65, kFarMinGroupMono = 129;
-// Systems of up to this many particles are not expanded: their trees are too shallow to gain
-// (512 systems of 1024..65536 particles: 13.0 -> 13.1 ms per step with it; one of 2^20: 4.05 -> 3.87).
+// Systems of up to this many particles are not expanded (each by its own size, whatever else is in the
+// batch): their trees are shallow, and the expansion is a launch of serial chains.  Force + expansion,
+// n_group 256, without / with it, Plummer and clustered: 10^5 particles 0.43 / 0.46 and 0.41 / 0.40 ms,
+// 131072 0.49 / 0.51 and 0.48 / 0.47, 2 10^5 0.59 / 0.61 and 0.62 / 0.58, 5 10^5 1.25 / 1.21 and
+// 1.36 / 1.20; 40000, n_group 512, 0.41 / 0.47 and 0.56 / 0.55.
 constexpr int64_t kFarMaxDirect = 131072;
 
 // Geometry of a group's expansion (written with the group's box).  thr2 < 0: no expansion (the

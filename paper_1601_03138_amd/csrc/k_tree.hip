@@ -490,9 +490,9 @@ k_group_geom(const uint32_t *ngroups, int nsys, const int64_t *off, Cells c,
                 // squared box radius: half its diagonal, in units of the cell side and in length
                 const double r2 = ldexp(d2, 2 * ((int)l - 22));
                 f.thr2 = (float)(r2 * side * side * (double)(kFarRatio * kFarRatio));
-                // one softening; scales whose powers stay in range; a deep enough tree
+                // a large system; one softening; scales whose powers stay in range; a deep enough tree
                 const double span = (double)kFarRatio * kFarSpan;
-                if (wide || emin != emax || !(f.inv_h > 1e-15 && f.inv_h < 1e15) ||
+                if (off[slo + 1] - off[slo] <= kFarMaxDirect || wide || emin != emax || !(f.inv_h > 1e-15 && f.inv_h < 1e15) ||
                     !(f.e2 < 1e8f) || r2 * span * span > ldexp(1.0, 2 * (int)l))
                     f.thr2 = -1.0f;
                 g.far[gi] = f;

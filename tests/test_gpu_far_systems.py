@@ -1,0 +1,31 @@
+"""The far-field expansion in batches of systems: it depends on a system's own size, so the FP32 forces
+of a system do not change with the company it is evaluated in."""
+import numpy as np
+import pytest
+
+from paper_1601_03138_amd import fdx
+from paper_1601_03138_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+def test_small_system_beside_a_large_one(persistent):
+    small = I.clustered(n_background=50001, n_clusters=8, n_per_cluster=6250, seed=11, eps=1e-3)
+    large = I.clustered(n_background=70001, n_clusters=8, n_per_cluster=8750, seed=12, eps=1e-3)
+    with fdx.Context(0) as ctx:
+        ctx.set_particles(small)
+        ctx.calc_force(0.5, 8, 256, 0.0, quad=True, fp32=True, persistent=persistent)
+        alone, g = ctx.forces(), ctx.groups()
+        perm = ctx.tree()["perm"].astype(np.int64)
+        assert np.array_equal(ctx.near_counts(), ctx.list_counts()[1])
+        ctx.set_particles(I.concat([small, large]))
+        ctx.calc_force(0.5, 8, 256, 0.0, quad=True, fp32=True, persistent=persistent)
+        both, near, ns = ctx.forces(), ctx.near_counts(), ctx.list_counts()[1]
+    n_groups = len(g["count"])
+    assert np.array_equal(near[:n_groups], ns[:n_groups]) and np.any(near[n_groups:] < ns[n_groups:])
+    # the last up to three groups share a run of the walk with the other system's first ones, which
+    # orders their lists differently
+    same = perm[:int(g["begin"][n_groups // 4 * 4]) if n_groups % 4 else small.n]
+    assert len(same) > small.n - 3 * 256
+    assert np.array_equal(alone[same], both[same])
