@@ -103,16 +103,14 @@ Cells cells_view(fdx_ctx *c) {
 static bool use_far(const fdx_ctx *c) {
     if (!(c->flags & FDX_FP32REL) || (c->flags & FDX_FUSED) || c->cutoff > 0) return false;
     if (c->n_group < ((c->flags & FDX_QUAD) ? kFarMinGroup : kFarMinGroupMono)) return false;
-    int64_t largest = 0;
-    for (int s = 0; s < c->nsys && (size_t)s + 1 < c->sys_off_h.size(); s++)
-        largest = std::max(largest, c->sys_off_h[s + 1] - c->sys_off_h[s]);
-    return largest > kFarMaxDirect;
+    return c->largest_sys > kFarMaxDirect;
 }
 
 Groups groups_view(fdx_ctx *c) {
     Groups g;
     g.cell = c->g_cell.p; g.begin = c->g_begin.p; g.count = c->g_count.p; g.sys = c->g_sys.p;
-    g.box = c->g_box.p; g.centre = c->g_centre.p; g.wide = c->g_wide.p; g.far = use_far(c) ? c->g_far.p : nullptr; g.cap = c->group_cap;
+    g.box = c->g_box.p; g.centre = c->g_centre.p; g.wide = c->g_wide.p; g.cap = c->group_cap;
+    g.far = use_far(c) ? c->g_far.p : nullptr;
     return g;
 }
 
@@ -605,8 +603,7 @@ int fdx_set_particles(fdx_ctx *c, int64_t n, const double *x, const double *y, c
     c->gen++;
     ext_invalidate(c);
     c->n = n;
-    c->nsys = n_sys;
-    c->sys_off_h = off;
+    c->set_systems(off);
     c->eps_given = eps != nullptr;
     c->borrowed = mem_kind == FDX_MEM_DEVICE;
     const size_t N = (size_t)n;

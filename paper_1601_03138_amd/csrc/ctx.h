@@ -61,6 +61,14 @@ struct fdx_ctx {
     // read per particle less)
     bool eps_per_system = false;
     std::vector<int64_t> sys_off_h;
+    int64_t largest_sys = 0;       // particles of the largest system
+    void set_systems(const std::vector<int64_t> &off) {
+        nsys = (int)off.size() - 1;
+        sys_off_h = off;
+        largest_sys = 0;
+        for (int s = 0; s < nsys; s++)
+            if (off[s + 1] - off[s] > largest_sys) largest_sys = off[s + 1] - off[s];
+    }
     fdx::DBuf<double> ox, oy, oz, ovx, ovy, ovz, om, oeps;       // owned copies
     double *x = nullptr, *y = nullptr, *z = nullptr, *vx = nullptr, *vy = nullptr,
            *vz = nullptr, *m = nullptr, *eps = nullptr;    // active arrays

@@ -372,8 +372,7 @@ int fdx_exchange_particles(fdx_ctx *c) {
     HIPCHK(c, c->cube.ensure(4 * (size_t)D));
     if (D > 1 && D <= 65536) HIPCHK(c, c->sys_carry.ensure(2 * N));
     HIPCHK(c, hipStreamSynchronize(s));        // dom_off is a host vector
-    c->nsys = D;
-    c->sys_off_h = d->dom_off;
+    c->set_systems(d->dom_off);
     c->have_force = false;
     c->have_lists = false;
     c->have_counts = false;

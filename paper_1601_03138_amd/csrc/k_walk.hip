@@ -262,7 +262,8 @@ constexpr int kFront = 224;             // frontier cells kept per wave
 // Up to this many groups (two waves for each that the chip holds) every group has a wave, which
 // repeats its run's first walk; beyond, a run has one.  Latency bound when few: a walk is a
 // serial chain of stack pops.  Fill walk, a wave per run / per group: 298 groups (4096 particles)
-// 77 / 34 us, 1500 groups 88 / 36 us, 14210 groups 252 / 210 us, 83047 groups 575 / 770 us.
+// 77 / 34 us, 1500 groups 88 / 36 us, 14210 groups 252 / 210 us, 83047 groups 575 / 770 us; both walks,
+// 13624 groups 335 / 295 us, 16467 280 / 278, 19385 359 / 365, 27401 437 / 487, 51117 562 / 759.
 constexpr uint32_t kSplitGroups = 16384;
 
 // the opening test at the box's far corners: false means every box inside [bmin, bmax] opens

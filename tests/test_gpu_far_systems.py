@@ -29,3 +29,21 @@ def test_small_system_beside_a_large_one(persistent):
     same = perm[:int(g["begin"][n_groups // 4 * 4]) if n_groups % 4 else small.n]
     assert len(same) > small.n - 3 * 256
     assert np.array_equal(alone[same], both[same])
+
+
+def test_systems_redrawn_by_an_exchange():
+    # whether anything may be expanded follows the systems that an exchange of particles makes
+    one = I.clustered(n_background=90001, n_clusters=8, n_per_cluster=11250, seed=13, eps=1e-3)
+
+    def expanded(ctx):
+        ctx.calc_force(0.5, 8, 256, 0.0, quad=True, fp32=True)
+        return int(np.sum(ctx.near_counts() < ctx.list_counts()[1]))
+    with fdx.Context(0) as ctx:
+        ctx.set_particles(one)
+        assert expanded(ctx) > 0
+        ctx.decompose(2, 1, 1, 10000, seed=3)
+        ctx.exchange_particles()
+        assert ctx.stats()["n_sys"] in (0, 2) and expanded(ctx) == 0
+        ctx.decompose(1, 1, 1, 10000, seed=4)
+        ctx.exchange_particles()
+        assert expanded(ctx) > 0
