@@ -17,6 +17,7 @@
 
 #include "dev_util.h"
 #include "far_field.h"
+#include "far_partition.h"
 #include "fdx_internal.h"
 
 namespace fdx {
@@ -25,10 +26,8 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kScan = 2;                          // list entries per lane and block
-constexpr uint32_t kBlock = kScan * kWave;        // entries read together
-constexpr uint32_t kQueue = kBlock + kWave;       // a block on top of a part-filled round
-constexpr uint32_t kHeld = 4 * kBlock;            // ids waiting for a free slot, per kind
+constexpr int kScan = kFarBlock / kWave;          // list entries per lane and block
+constexpr uint32_t kQueue = kFarBlock + kWave;    // a block on top of a part-filled round
 
 struct FarArgs {
     const uint32_t *ngroups, *gcount;
@@ -84,7 +83,7 @@ __global__ void __launch_bounds__(kThreads, 3)
 k_far(FarArgs a) {
     __shared__ float4 qx_all[kWaves][kQueue];          // to be expanded
     __shared__ uint32_t qi_all[QUAD ? kWaves : 1][QUAD ? kQueue : 1];
-    __shared__ uint32_t held_all[kWaves][2][kHeld];    // ids to be written back: near, far
+    __shared__ uint32_t held_all[kWaves][2][kFarHeld];    // ids to be written back: near, far
     const int w = threadIdx.x / kWave, lane = lane_id();
     const uint64_t lt = lanemask_lt();
     const uint32_t G = min(*a.ngroups, a.gmax);
@@ -118,22 +117,8 @@ k_far(FarArgs a) {
         const float i = __builtin_amdgcn_rsqf(fmaf(z, z, fmaf(y, y, fmaf(x, x, f.e2))));
         acc.template add<QUAD>(x, y, z, i, e.w, q);
     };
-    // The list is partitioned in place, near entries from its front and far ones from its back,
-    // in blocks that are read ahead from either end.  Entries read and not yet written back are
-    // as many as the slots read and not yet overwritten; after each block as many ids as have a
-    // free slot on their side are written, which leaves at most one kind waiting, and the next
-    // block to be read comes from that kind's end.  A block is chosen two blocks before it is
-    // sorted in, so at most three blocks of one kind wait.
-    uint32_t lo = 0, hi = ns;                      // entries not yet chosen: [lo, hi)
-    uint32_t held[2] = {0, 0}, room[2] = {0, 0}, put[2] = {0, 0};
-    struct Block { uint32_t start, len, back; };
-    auto choose = [&](uint32_t back) {
-        Block b;
-        b.len = min(kBlock, hi - lo);
-        b.back = back;
-        if (back) { hi -= b.len; b.start = hi; } else { b.start = lo; lo += b.len; }
-        return b;
-    };
+    FarPartition part(ns);
+    using Block = FarPartition::Block;
     auto load_ids = [&](const Block &b, uint32_t (&id)[kScan]) {
 #pragma unroll
         for (int k = 0; k < kScan; k++) {
@@ -149,7 +134,7 @@ k_far(FarArgs a) {
         }
     };
     uint32_t cnt = 0;                              // queued for expansion, the same in every lane
-    Block b0 = choose(0), b1 = choose(0);
+    Block b0 = part.choose(0), b1 = part.choose(0);
     uint32_t id0[kScan], id1[kScan];
     double2 u0[kScan], v0[kScan];
     load_ids(b0, id0);
@@ -168,21 +153,21 @@ k_far(FarArgs a) {
             if (in) {
                 // the entries of a block are its first lanes, so the near ones before a lane are
                 // the lanes before it less the far ones
-                held_all[w][far ? 1 : 0][far ? held[1] + rank : held[0] + (uint32_t)lane - rank] =
-                    id0[k];
+                const uint32_t at = far ? part.held[1] + rank : part.held[0] + (uint32_t)lane - rank;
+                held_all[w][far ? 1 : 0][at] = id0[k];
             }
             if (far) {
                 qx_all[w][cnt + rank] = make_float4(px, py, pz, (float)u0[k].x);
                 if (QUAD) qi_all[w][cnt + rank] = id0[k];
             }
             cnt += nf;
-            held[0] += min(kWave + 0u, b0.len > (uint32_t)(k * kWave) ? b0.len - k * kWave : 0u) - nf;
-            held[1] += nf;
+            part.held[0] += min(kWave + 0u, b0.len > (uint32_t)(k * kWave) ? b0.len - k * kWave : 0u) - nf;
+            part.held[1] += nf;
         }
-        room[b0.back] += b0.len;
+        const uint32_t back = part.sorted(b0);
         wave_barrier();
         // the next block: ids long arrived, its centres of mass on the way during the expansion
-        const Block b2 = choose(held[1] > room[1] ? 1u : 0u);
+        const Block b2 = part.choose(back);
         b0 = b1;
         b1 = b2;
 #pragma unroll
@@ -192,14 +177,10 @@ k_far(FarArgs a) {
         // ids back into free slots
 #pragma unroll
         for (int c = 0; c < 2; c++) {
-            const uint32_t n = min(held[c], room[c]);
-            held[c] -= n;
-            for (uint32_t i = (uint32_t)lane; i < n; i += kWave) {
-                const uint32_t slot = c ? ns - 1u - (put[1] + i) : put[0] + i;
-                spj[slot] = held_all[w][c][held[c] + i];
-            }
-            put[c] += n;
-            room[c] -= n;
+            const uint32_t n = part.ready(c);
+            for (uint32_t i = (uint32_t)lane; i < n; i += kWave)
+                spj[part.slot(c, i)] = held_all[w][c][part.held[c] + i];
+            part.written(c, n);
         }
         while (cnt >= (uint32_t)kWave) {
             cnt -= kWave;
@@ -210,11 +191,9 @@ k_far(FarArgs a) {
     // every slot is read: what is left goes to the slots in between
 #pragma unroll
     for (int c = 0; c < 2; c++)
-        for (uint32_t i = (uint32_t)lane; i < held[c]; i += kWave) {
-            const uint32_t slot = c ? ns - 1u - (put[1] + i) : put[0] + i;
-            spj[slot] = held_all[w][c][i];
-        }
-    if (lane == 0) a.near[gi] = put[0] + held[0];
+        for (uint32_t i = (uint32_t)lane; i < part.held[c]; i += kWave)
+            spj[part.slot(c, i)] = held_all[w][c][i];
+    if (lane == 0) a.near[gi] = part.put[0] + part.held[0];
     if ((uint32_t)lane < cnt) expand((uint32_t)lane);
     acc.fold();
     // the sums over the wave, the same in every lane
