@@ -31,12 +31,15 @@ sys.path.insert(0, ROOT)
 PEAK_FP32_TFLOPS = 157.3
 PEAK_FP64_TFLOPS = 78.6
 # Algorithmic flops per interaction of the force kernels (FMA = 2, rsqrt = 1), counted from
-# the formulas they evaluate: particle 20; superparticle monopole 20, quadrupole 54.  They are
-# counted for every listed interaction; the FP32 path evaluates a group's far superparticles through
-# one polynomial instead of pair by pair, so its rate can pass what the pair loop issues.
+# the formulas they evaluate: particle 20; superparticle monopole 20, quadrupole 54.
 FLOPS_PP = 20
 FLOPS_PC_MONO = 20
 FLOPS_PC_QUAD = 54
+# The FP32 path sums a group's far superparticles in one polynomial: flops per far superparticle (46
+# coefficients) and per member that evaluates it, counted the same way from far_field.h
+FLOPS_FAR_MONO = 231
+FLOPS_FAR_QUAD = 374
+FLOPS_FAR_MEMBER = 205
 
 WORKLOADS = {
     # name: (n_group, theta, quad, dt); the clustered and ensemble workloads are defined with
@@ -73,23 +76,38 @@ def force_flops(st, quad):
         FLOPS_PC_QUAD if quad else FLOPS_PC_MONO)
 
 
+def executed_flops(st, quad, n_near, n_spj, count):
+    """Flops that a force evaluation executed: its particle pairs, the superparticles that each group
+    took pair by pair (n_near of n_spj), the rest through the group's polynomial, which each of its
+    `count` members evaluates."""
+    near, spj, count = (np.asarray(v, dtype=np.int64) for v in (n_near, n_spj, count))
+    far = spj - near
+    return (st["n_interactions_pp"] * FLOPS_PP
+            + int(np.sum(near * count)) * (FLOPS_PC_QUAD if quad else FLOPS_PC_MONO)
+            + int(np.sum(far)) * (FLOPS_FAR_QUAD if quad else FLOPS_FAR_MONO)
+            + int(np.sum(count[far > 0])) * FLOPS_FAR_MEMBER)
+
+
 def force_source_sha():
-    """sha256 over the force kernel's sources (k_force.hip, then interact.h, byte for byte):
-    a traffic summary counts only for the code it was measured on."""
+    """sha256 over the sources of the force phase (byte for byte, those that there are): a traffic
+    summary counts only for the code it was measured on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("k_force.hip", "interact.h"):
+    for k, f in enumerate(("k_force.hip", "interact.h", "k_far.hip", "far_field.h", "far_partition.h",
+                           "group_queue.h", "group_items.h", "dev_util.h")):
         try:
             h.update(open(os.path.join(ROOT, "paper_1601_03138_amd", "csrc", f), "rb").read())
         except OSError:
-            return None
+            if k < 2:
+                return None
     return h.hexdigest()
 
 
 def read_traffic(kernel_tag: str, shape: str, launch: str):
-    """HBM bytes per launch of the force kernel measured by rocprofv3 counters, if a summary
-    for the current kernel source, this shape and this launch is committed under profiles/
-    (files <kernel_tag>_<shape>_traffic.txt; else None)."""
+    """HBM bytes per evaluation of the force kernel, and of the far-field kernel where the summary
+    gives them, measured by rocprofv3 counters, if a summary for the current kernel sources, this
+    shape and this launch is committed under profiles/ (files <kernel_tag>_<shape>_traffic.txt;
+    else None)."""
     import glob
     sha = force_source_sha()
     if sha is None:
@@ -104,7 +122,8 @@ def read_traffic(kernel_tag: str, shape: str, launch: str):
                 or vals.get("launch") != launch):
             continue
         try:
-            return float(vals["hbm bytes per launch"])
+            return float(vals["hbm bytes per launch"]) + float(
+                vals.get("far-field kernel hbm bytes per launch", 0.0))
         except (KeyError, ValueError):
             return None
     return None
@@ -336,14 +355,17 @@ def main():
             phases.append({k: st[k] for k in st if k.startswith("t_")})
     st = ctx.stats()
     mean_force_ms = float(np.mean(t_force))
-    achieved = float(np.mean(flops)) / (mean_force_ms / 1e3) / 1e12
+    # executed work: the last evaluation's share of its listed interactions
+    n_near, n_spj = ctx.near_counts(), ctx.list_counts()[1]
+    far_pairs = int(np.sum((n_spj - n_near).astype(np.int64) * ctx.groups()["count"]))
+    executed = executed_flops(st, quad, n_near, n_spj, ctx.groups()["count"]) / force_flops(st, quad)
+    achieved = float(np.mean(flops)) * executed / (mean_force_ms / 1e3) / 1e12
     phase_ms = {k[2:]: round(float(np.mean([p[k] for p in phases])), 4) for k in phases[0]}
     shape = ctx.shape_name(st["shape"])
     # algorithmic bytes of the HBM-bound phases (per particle unless stated): keys = bbox read
     # 24 + key kernel read 32 (x, y, z, m) / write 12 (key, index) + 32 ((x, y, z, m) record
-    # for the sorted gather); sort = 32 per radix pass (8 B
-    # histogram read, 12 B pair read and written) + sorted gather (4 perm + 32 record + 32 out
-    # + 8 eps + 4 inverse); walk = the 4-byte list entries written by the fill pass
+    # for the sorted gather); sort = 8 for the histogram of all digits, 24 per radix pass (12 B
+    # pair read and written) + sorted gather (4 perm + 32 record + 32 out + 8 eps + 4 inverse); walk = the 4-byte list entries written by the fill pass
     passes = 8 + (0 if ps.n_sys <= 1 else (int(np.ceil(np.log2(ps.n_sys))) + 7) // 8)
     gbs = lambda b, ms: round(b / (ms / 1e3) / 1e9, 1) if ms > 0 else None
     # tree = 30 B per particle (keys read by the level, count and emit passes) + 60 B per
@@ -351,7 +373,7 @@ def main():
     # particle + 1 B leaf level written and read
     ncell = int(st["n_cells"])
     phase_gbs = {"keys": gbs(100 * ps.n, phase_ms["keys"]),
-                 "sort": gbs((32 * passes + 80) * ps.n, phase_ms["sort"]),
+                 "sort": gbs((8 + 24 * passes + 80) * ps.n, phase_ms["sort"]),
                  "tree": gbs(30 * ps.n + 60 * ncell, phase_ms["tree"]),
                  "moments": gbs(160 * ncell, phase_ms["moments"]),
                  "groups": gbs(18 * ps.n, phase_ms["groups"]),
@@ -630,14 +652,17 @@ def main():
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
                      "traffic": traffic,
                      "kernel": ("k_fused<float, quad> (walk + force, one launch)" if args.fused
-                                else f"k_force_persistent<float, quad> {shape}" if persistent
-                                else f"k_force_direct<float, quad> {shape}"),
+                                else ("k_far<quad> + " if far_pairs else "")
+                                + (f"k_force_persistent<float, quad> {shape}" if persistent
+                                   else f"k_force_direct<float, quad> {shape}")),
                      "kernel_ms": round(mean_force_ms, 3),
                      "interactions_per_launch": int(st["n_interactions_pp"] + st["n_interactions_pc"]),
                      "interactions_per_s": round((st["n_interactions_pp"] + st["n_interactions_pc"])
                                                  / (mean_force_ms / 1e3), -8),
-                     "flops_counted_for": "every listed interaction (far superparticles are "
-                                          "evaluated through one polynomial per group)",
+                     "far_interactions_per_launch": far_pairs,
+                     "flops_counted_for": "executed work: every particle pair, near superparticles "
+                                          "pair by pair, far ones once per group and the "
+                                          "polynomial once per member",
                      "flops_per_interaction": {"pp": FLOPS_PP,
                                                "pc": FLOPS_PC_QUAD if quad else FLOPS_PC_MONO}},
         "cpu_baseline": cpu,
