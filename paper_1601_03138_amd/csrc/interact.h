@@ -1,5 +1,5 @@
 // Softened-gravity interaction functions shared by the force kernels (k_force.hip) and the
-// one-launch walk + force kernel (k_fused.hip).
+// one-launch walk + force kernel (k_fused.hip), and the sums of the force kernels (k_cut.hip too).
 //
 // Particle term (equation ParticleParticleNbody, G = 1):
 //   a_i += m_j (r_j - r_i) / (|r_j - r_i|^2 + eps_i^2)^{3/2},  phi_i -= m_j / (...)^{1/2}
@@ -29,6 +29,22 @@ __device__ __forceinline__ double rsqrt_t(double x) {
     const double r = fma(-(x * y), y, 1.0);
     return fma(y * r, 0.5, y);
 }
+
+// Kahan accumulator (FP32) or plain sum (FP64)
+template <class T> struct Acc {
+    T s = 0;
+    __device__ __forceinline__ void add(T v) { s += v; }
+    __device__ __forceinline__ double val() const { return (double)s; }
+};
+template <> struct Acc<float> {
+    float s = 0.f, c = 0.f;
+    __device__ __forceinline__ void add(float v) {
+        const float y = v - c, t = s + y;
+        c = (t - s) - y;
+        s = t;
+    }
+    __device__ __forceinline__ double val() const { return (double)s - (double)c; }
+};
 
 template <class T>
 __device__ __forceinline__ void pp(const typename V4<T>::t &J, T xi, T yi, T zi, T e2, T &ax,

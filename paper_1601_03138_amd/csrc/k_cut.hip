@@ -62,22 +62,6 @@ __device__ __forceinline__ float cut_dist(float r2) { return __builtin_amdgcn_sq
 // with the general sqrt, 2.05 with this one.
 __device__ __forceinline__ double cut_dist(double r2) { return sqrt_pos(r2 + 1e-290); }
 
-// Kahan accumulator (FP32) or plain sum (FP64)
-template <class T> struct Acc {
-    T s = 0;
-    __device__ __forceinline__ void add(T v) { s += v; }
-    __device__ __forceinline__ double val() const { return (double)s; }
-};
-template <> struct Acc<float> {
-    float s = 0.f, c = 0.f;
-    __device__ __forceinline__ void add(float v) {
-        const float y = v - c, t = s + y;
-        c = (t - s) - y;
-        s = t;
-    }
-    __device__ __forceinline__ double val() const { return (double)s - (double)c; }
-};
-
 template <class T>
 struct CutSmem {
     using V = typename V4<T>::t;

@@ -48,27 +48,10 @@ struct KArgs {
     const uint32_t *ngroups;
     double4 *fs;
     DevStatus *st;
-    uint32_t G;
-    uint32_t run;         // direct launch: consecutive groups per XCD              // groups (direct launch); persistent kernels read *ngroups
+    uint32_t G;              // groups (direct launch); persistent kernels read *ngroups
+    uint32_t run;            // direct launch: consecutive groups per XCD
     const uint32_t *near;    // FP32 with a far-field expansion: near superparticles per group
                              // (kNone: not expanded), or null
-};
-
-// Kahan accumulator (FP32) or plain sum (FP64)
-template <class T> struct Acc {
-    T s = 0;
-    __device__ __forceinline__ void add(T v) { s += v; }
-    __device__ __forceinline__ double val() const { return (double)s; }
-};
-template <> struct Acc<float> {
-    float s = 0.f, c = 0.f;
-    __device__ __forceinline__ void add(float v) {
-        float y = v - c;
-        float t = s + y;
-        c = (t - s) - y;
-        s = t;
-    }
-    __device__ __forceinline__ double val() const { return (double)s - (double)c; }
 };
 
 template <class T, int NT, int IPL, int JT>
