@@ -5,10 +5,11 @@
 // launch per digit: one kernel histograms every digit place at once (the counts do not
 // depend on the order), and each pass takes tiles by ticket, ranks the tile with ballot-based
 // multisplit (stable), adds the counts of the tiles before it by looking back over their
-// published sums, and writes each digit's run of the tile, laid out in LDS, contiguously.  With
-// several systems (at most 2^16) and a carry buffer, a 16-bit copy of each element's system
-// id travels with it through the key passes, so the system-id passes read their digit in
-// order instead of gathering it through the permutation.
+// published sums (the single-pass scan with decoupled look-back, Merrill & Garland 2016), and
+// writes each digit's run of the tile, laid out in LDS, contiguously.  With several systems
+// (at most 2^16) and a carry buffer, a 16-bit copy of each element's system id travels with it
+// through the key passes, so the system-id passes read their digit in order instead of
+// gathering it through the permutation.
 //
 // A pass moves 24 B per element (12 read, 12 written) and is bound by HBM and by the latency of
 // the chain load -> rank -> look back -> write.  Whole sort of 8 key passes, against a histogram,
