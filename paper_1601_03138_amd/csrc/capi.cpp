@@ -3,8 +3,9 @@
 // One force evaluation is one pass over: root cubes and keys -> radix sort -> sorted
 // particle gather -> level-by-level octree -> bottom-up moments -> groups -> walk (count,
 // scan, fill) -> force kernel -> return of forces to the caller's order.  Everything runs on
-// the bound stream; the host waits for the device status three times per evaluation: after the groups
-// (bad input, tree overflow, group count), after the counting walk to size the list buffer, and at the end for the counters.
+// the bound stream; the host waits for the device status three times per evaluation: after the
+// groups (bad input, tree overflow, group count), after the counting walk to size the list buffer,
+// and at the end for the counters.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
